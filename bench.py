@@ -116,7 +116,7 @@ _GEMM_EPI = {"gemm_qkv": (0, 0), "gemm_o": (2, 4), "gemm_ffn1": (1, 1), "gemm_ff
 
 def _gemm_kernel(bm, bn, wgs, epi, n, f32):
     if (bm, bn) == (256, 256):
-        return f"gemm_sched_kernel<256, 256, 2, 4, 32, {epi}, 1, 2>"
+        return f"gemm_persist_kernel<{epi}>"
     if (bm, bn) == (128, 128):
         return f"gemm_sched_kernel<128, 128, 2, 2, 32, {epi}, 2, 2>"
     if (bm, bn) == (64, 128):

@@ -6,7 +6,7 @@
 // either an fp32 matrix or a LayerNorm output rebuilt from its pre-norm rows and
 // row statistics (Residual in kernels.h).
 //
-// Two kernel families; launch_gemm plans each product (plan_gemm: one launch, or a
+// Three kernels; launch_gemm plans each product (plan_gemm: one launch, or a
 // launch of large tiles over whole rounds plus one of small tiles over the remaining rows):
 //   gemm_kernel        register-staged k-slabs, 16 x 16 x 32 MFMA blocks; for N that
 //                      is an odd multiple of 64;
@@ -15,7 +15,9 @@
 //                      (operand fragments double-buffered in registers, MFMAs of the
 //                      last k-step of a slab issued after the slab barrier) and an
 //                      epilogue staged through LDS for full-line stores; tiles of
-//                      256 x 256, 128 x 128, 64 x 128 and 64 x 64.
+//                      128 x 128, 64 x 128 and 64 x 64;
+//   gemm_persist_kernel  256 x 256 tiles, one persistent work-group per CU whose two wave
+//                      groups alternate between reading fragments and multiplying.
 //
 // LDS layout. A k-slab row of 64 bf16 is eight 16-byte chunks; the chunk index
 // is XOR-swizzled with the row so the rows one MFMA operand read touches fall on
@@ -38,6 +40,20 @@
 #include "kernels.h"
 
 namespace elis {
+
+// Compute units of the current device (the launch-time model below needs it). A device property,
+// looked up once per device; the cache is safe to read and fill from several host threads.
+int device_cus() {
+    static std::atomic<int> cus[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    int v = cus[dev].load(std::memory_order_relaxed);
+    if (v == 0) {
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
+        cus[dev].store(v, std::memory_order_relaxed);
+    }
+    return v;
+}
 
 namespace {
 
@@ -254,6 +270,111 @@ __device__ __forceinline__ void grouped_tile(int t, int tiles_m, int tiles_n, in
 // the plain (row & 7) form conflicts 4-way on the 32-row reads.
 
 
+// Bytes between the staged rows of a wave tile TN columns wide (16 bytes of padding).
+template <int TN, int EPI>
+constexpr int wave_tile_pitch() {
+    return TN * (kF32Out<EPI> ? 4 : 2) + 16;
+}
+
+// Epilogue through LDS: each wave stages one 32-row block row of its output tile (bias,
+// activation / residual applied), then writes it back as whole rows, 16 bytes per lane,
+// so every store instruction covers full cache lines. bf16 outputs are stored
+// non-temporally: they stream past the caches that hold the next tiles' operands (1% per
+// predictor pass, up to 9% for a single GEMM). fp32 outputs (the pre-LayerNorm rows) are
+// stored normally: the LayerNorm that reads them next then finds part of them in the
+// memory-side cache (LayerNorm 21.4 -> 20.0 us at 24K tokens, 0.8% per pass).
+// acc[i][j]: the 32 x 32 block at rows mw + 32 i, columns nw + 32 j, of a wave tile FM x FN blocks
+// large; stg: 32 * wave_tile_pitch bytes of LDS of this wave's own.
+template <int FM, int FN, int EPI>
+__device__ __forceinline__ void store_wave_tile(const f32x16 (&acc)[FM][FN], char* stg, const float* __restrict__ bias,
+                                                const Residual& res, void* __restrict__ out, int mw, int nw, int M,
+                                                int N, int lane) {
+    constexpr int TN = 32 * FN;
+    const int rl = lane & 31, kg = lane >> 5;
+    constexpr bool F32OUT = kF32Out<EPI>;
+    constexpr int EB = F32OUT ? 4 : 2;          // output element bytes
+    constexpr int ROWB = TN * EB;               // bytes of one wave-tile row
+    constexpr int PITCH = wave_tile_pitch<TN, EPI>();
+    constexpr int LPR = ROWB / 16;              // lanes per row on read-back
+    constexpr int RPR = kWave / LPR;            // rows per read-back instruction
+    // On read-back a lane always covers the same 16 output bytes of a row: columns nl ...
+    const int ch = lane % LPR;
+    const int nl = nw + ch * (16 / EB);
+    f32x4 gl, bl;  // LayerNorm g, b of those columns (LayerNorm-form residual)
+    if constexpr (kResLn<EPI>) {
+        gl = *reinterpret_cast<const f32x4*>(res.g + nl);
+        bl = *reinterpret_cast<const f32x4*>(res.b + nl);
+    }
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int col = j * 32 + 8 * q + 4 * kg;
+                f32x4 v;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = acc[i][j][4 * q + r];
+                v += *reinterpret_cast<const f32x4*>(bias + nw + col);
+                if constexpr (F32OUT) {
+                    *reinterpret_cast<f32x4*>(stg + rl * PITCH + col * 4) = v;
+                } else {
+                    if constexpr (EPI == ELIS_EPI_BIAS_GELU_BF16) {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) v[c] = gelu_erf(v[c]);
+                    }
+                    u32x2 pk;
+                    pk[0] = pack_bf16x2(v[0], v[1]);
+                    pk[1] = pack_bf16x2(v[2], v[3]);
+                    *reinterpret_cast<u32x2*>(stg + rl * PITCH + col * 2) = pk;
+                }
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+        asm volatile("" ::: "memory");
+        constexpr int NRR = 32 / RPR;  // read-back rows per lane per block row
+        if constexpr (F32OUT) {
+            // All residual vectors (and row statistics) of the block row are requested first.
+            f32x4 hv[NRR];
+            float2 sv[NRR];
+#pragma unroll
+            for (int rr = 0; rr < NRR; ++rr) {
+                const int m = mw + i * 32 + rr * RPR + lane / LPR;
+                const int mc = m < M ? m : M - 1;  // rows past the end load a valid row, store nothing
+                hv[rr] = *reinterpret_cast<const f32x4*>(res.x + static_cast<size_t>(mc) * N + nl);
+                if constexpr (kResLn<EPI>) sv[rr] = res.stats[mc];
+            }
+#pragma unroll
+            for (int rr = 0; rr < NRR; ++rr) {
+                const int row = rr * RPR + lane / LPR;
+                const int m = mw + i * 32 + row;
+                const u32x4 d = *reinterpret_cast<const u32x4*>(stg + row * PITCH + ch * 16);
+                if (m < M) {
+                    f32x4 h = hv[rr];
+                    if constexpr (kResLn<EPI>) {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) h[c] = fmaf((h[c] - sv[rr].x) * sv[rr].y, gl[c], bl[c]);
+                    }
+                    const f32x4 v = __builtin_bit_cast(f32x4, d) + h;
+                    *reinterpret_cast<f32x4*>(static_cast<float*>(out) + static_cast<size_t>(m) * N + nl) = v;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int rr = 0; rr < NRR; ++rr) {
+                const int row = rr * RPR + lane / LPR;
+                const int m = mw + i * 32 + row;
+                const u32x4 d = *reinterpret_cast<const u32x4*>(stg + row * PITCH + ch * 16);
+                if (m < M) __builtin_nontemporal_store(d, reinterpret_cast<u32x4*>(static_cast<uint16_t*>(out) + static_cast<size_t>(m) * N + nl));
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+        asm volatile("" ::: "memory");
+    }
+}
+
 template <int BM, int BN, int WM, int WN, int MI, int EPI, int OCC = 1, int S = 2>
 __global__ __launch_bounds__(WM* WN* kWave) __attribute__((amdgpu_waves_per_eu(OCC * WM * WN / 4, OCC * WM * WN / 4))) void gemm_sched_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, const float* __restrict__ bias,
@@ -384,130 +505,360 @@ __global__ __launch_bounds__(WM* WN* kWave) __attribute__((amdgpu_waves_per_eu(O
     for (; kt + 1 < KT; ++kt) slab(kt, W0_(), F_(), T_());
     slab(kt, W0_(), F_(), F_());
 
-    // Epilogue through LDS: each wave stages one 32-row block row of its output tile (bias,
-    // activation / residual applied), then writes it back as whole rows, 16 bytes per lane,
-    // so every store instruction covers full cache lines. bf16 outputs are stored
-    // non-temporally: they stream past the caches that hold the next tiles' operands (1% per
-    // predictor pass, up to 9% for a single GEMM). fp32 outputs (the pre-LayerNorm rows) are
-    // stored normally: the LayerNorm that reads them next then finds part of them in the
-    // memory-side cache (LayerNorm 21.4 -> 20.0 us at 24K tokens, 0.8% per pass).
+    static_assert(NW * 32 * wave_tile_pitch<TN, EPI>() <= S * STAGE * 2, "staging must fit in the stage buffers");
     static_assert(MI == 32, "staged epilogue assumes 32-row MFMA blocks");
-    constexpr bool F32OUT = kF32Out<EPI>;
-    constexpr int EB = F32OUT ? 4 : 2;          // output element bytes
-    constexpr int ROWB = TN * EB;               // bytes of one wave-tile row
-    constexpr int PITCH = ROWB + 16;            // padded LDS row pitch
-    constexpr int LPR = ROWB / 16;              // lanes per row on read-back
-    constexpr int RPR = kWave / LPR;            // rows per read-back instruction
-    static_assert(NW * 32 * PITCH <= S * STAGE * 2, "staging must fit in the stage buffers");
     block_sync_lds();  // every wave is done with the stage buffers
-    char* stg = reinterpret_cast<char*>(smem) + wid * 32 * PITCH;
-    // On read-back a lane always covers the same 16 output bytes of a row: columns nl ...
-    const int ch = lane % LPR;
-    const int nl = n0 + wn * TN + ch * (16 / EB);
-    f32x4 gl, bl;  // LayerNorm g, b of those columns (LayerNorm-form residual)
-    if constexpr (kResLn<EPI>) {
-        gl = *reinterpret_cast<const f32x4*>(res.g + nl);
-        bl = *reinterpret_cast<const f32x4*>(res.b + nl);
+    store_wave_tile<FM, FN, EPI>(acc, reinterpret_cast<char*>(smem) + wid * 32 * wave_tile_pitch<TN, EPI>(), bias, res,
+                                 out, m0 + wm * TM, n0 + wn * TN, M, N, lane);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Persistent 256 x 256 tiles, one work-group of 8 waves per CU; each wave owns a 128 x 64 block.
+//
+// k-loop. A 64-deep k-slab is four half-slabs in LDS (A rows / B rows that all waves read in the
+// same phase) and four phases, one per (A half, B half) quadrant of the wave block: 8 MFMAs each.
+// A phase is a memory part (LDS fragment reads, the direct loads of a half-slab two slabs ahead
+// into the slot just read, the wait for the half-slab the next phase reads) and an MFMA part, with
+// a barrier behind each. The two groups of four waves (one wave of each per SIMD) run one part
+// apart, so on every SIMD one wave multiplies while the other reads.
+//
+// Tiles. A work-group walks its tiles as one stream of slabs: the loads of the next tile's first
+// two slabs are in flight during a tile's last two slabs and land under its epilogue, whose
+// stores in turn drain under the next tile's first slabs (their waits are left out: those slabs
+// landed before the first store). Past the last tile the stream loads through empty buffer
+// resources (no memory access), so every slab runs the same code and wait counts.
+//
+// What bounds it. On full rounds the board's power limit: 8192 x 8192 x 8192 runs at 1,410 TFLOP/s
+// with normal operands (clock 1.6 GHz) and 1,980 with zeros (2.27 GHz), 80% of the matrix cores'
+// cycles both times. At k = 768 the epilogues take a quarter of the time (GELU's vector work and the
+// stores; with both left out 93,014 x 3,072 x 768 takes 342 us). Against the one-tile-per-launch
+// kernel with whole-slab waits that it replaces, in us (fp32 out with residual for n = 768):
+//   93,014 x 3,072 x 768 + GELU 489 -> 446    93,014 x 2,304 x 768 315 -> 284
+//   93,014 x 768 x 3,072        483 -> 453    21,760 x 3,072 x 768 + GELU 113 -> 104
+//   102,548 x 1,024 x 4,096     863 -> 800    21,760 x 768 x 3,072 100 -> 97
+// Two 256 x 128 work-groups per CU, which let one's epilogue run beside the other's k-loop, were
+// 2-10% slower: half again the operand bytes costs power, and the overlap gains nothing under it.
+template <int EPI>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_persist_kernel(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, const float* __restrict__ bias, Residual res,
+    void* __restrict__ out, int M, int N, int K, int group_m) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass has no buffer-resource type
+    constexpr int BM = 256, BN = 256, HALF = 128 * kBK, STAGE = 4 * HALF, STG = 2048;
+    constexpr bool F32OUT = kF32Out<EPI>;
+    constexpr int EB = F32OUT ? 4 : 2;
+    __shared__ __attribute__((aligned(1024))) uint16_t smem[2 * STAGE + 8 * STG];
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wid >> 2, wn = wid & 3;
+    const int tiles_n = N / BN, tiles_m = (M + BM - 1) / BM;
+    // This work-group's tiles: every XCD owns one contiguous range, dealt out to its work-groups.
+    const int tiles = tiles_m * tiles_n, xcd = blockIdx.x & 7, wgs = (static_cast<int>(gridDim.x) - xcd + 7) >> 3;
+    const int per = tiles >> 3, rem = tiles & 7;
+    const int t_end = xcd * per + (xcd < rem ? xcd : rem) + per + (xcd < rem ? 1 : 0);
+    int tile = t_end - per - (xcd < rem ? 1 : 0) + static_cast<int>(blockIdx.x >> 3);
+    auto origin = [&](int t, int& m0, int& n0) {
+        int tm, tn;
+        grouped_tile(t, tiles_m, tiles_n, group_m, tm, tn);
+        m0 = __builtin_amdgcn_readfirstlane(tm * BM);
+        n0 = __builtin_amdgcn_readfirstlane(tn * BN);
+    };
+
+    // Direct loads: wave w fills rows [16 w, 16 w + 16) of each half-slab with two wave-wide loads
+    // of 8 rows. Row r of A half h is row 128 (r / 64) + 64 h + r % 64 of the tile, of B half h
+    // column 64 (r / 32) + 32 h + r % 32, so a wave's quadrants make up a contiguous block. Rows
+    // past the end of A are outside the resource and read as zeros.
+    uint32_t oa[2][2], ob[2][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = wid * 16 + i * 8 + (lane >> 3), c = ((lane & 7) ^ swz(r)) * 8;
+            oa[h][i] = static_cast<uint32_t>((((r >> 6) * 128 + h * 64 + (r & 63)) * K + c) * 2);
+            ob[h][i] = static_cast<uint32_t>((((r >> 5) * 64 + h * 32 + (r & 31)) * K + c) * 2);
+        }
+    // The load stream: tile, k offset (bytes) and operands of the slab to request next.
+    int lt = tile, lk = 0, lm = 0, ln = 0, la_bytes = 0, lb_bytes = 0;
+    auto stream_tile = [&] {
+        const bool more = lt < t_end;
+        origin(more ? lt : t_end - 1, lm, ln);
+        la_bytes = more ? (M - lm < BM ? M - lm : BM) * K * 2 : 0;
+        lb_bytes = more ? BN * K * 2 : 0;
+    };
+    auto stream_next = [&] {
+        lk += la_bytes ? kBK * 2 : 0;  // an empty resource is read at offset 0 only
+        if (lk == K * 2) {
+            lk = 0;
+            lt += wgs;
+            stream_tile();
+        }
+    };
+    uint16_t* const my = smem + wid * 16 * kBK;
+    auto load_a = [&](int st, int h) {
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(A) + static_cast<size_t>(lm) * K, 0, la_bytes, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)(my + st + h * HALF + i * 8 * kBK), 16, oa[h][i], lk, 0, 0);
+    };
+    auto load_b = [&](int st, int h) {
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(B) + static_cast<size_t>(ln) * K, 0, lb_bytes, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)(my + st + (2 + h) * HALF + i * 8 * kBK), 16, ob[h][i], lk, 0, 0);
+    };
+
+    const int rl = lane & 31, kg = lane >> 5;
+    bf16x8 fa[2][4], fb[2][4];
+    // This lane's 16 bytes of a 32-row block at each 16-deep k-step, in the stage of the current slab.
+    int pa[4], pb[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        const int l = rl * kBK + (((ks * 2 + kg) ^ swz(rl)) * 8);
+        pa[ks] = wm * 64 * kBK + l;
+        pb[ks] = 2 * HALF + wn * 32 * kBK + l;
     }
+    auto read_a = [&](int h) {
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
+        for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
+            for (int i = 0; i < 2; ++i)
+                fa[i][ks] = *reinterpret_cast<const bf16x8*>(smem + pa[ks] + h * HALF + i * 32 * kBK);
+    };
+    auto read_b = [&](int h) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int col = j * MI + 8 * q + 4 * kg;
-                f32x4 v;
+        for (int ks = 0; ks < 4; ++ks) fb[h][ks] = *reinterpret_cast<const bf16x8*>(smem + pb[ks] + h * HALF);
+    };
+    f32x16 acc[4][2];
+    auto multiply = [&](int ha, int hb) {
+        __builtin_amdgcn_sched_barrier(0);
+        wait_lgkm<0>();
+        block_sync_lds();
+        __builtin_amdgcn_s_setprio(1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = acc[i][j][4 * q + r];
-                v += *reinterpret_cast<const f32x4*>(bias + n0 + wn * TN + col);
-                if constexpr (F32OUT) {
-                    *reinterpret_cast<f32x4*>(stg + rl * PITCH + col * 4) = v;
-                } else {
-                    if constexpr (EPI == ELIS_EPI_BIAS_GELU_BF16) {
+        for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) v[c] = gelu_erf(v[c]);
-                    }
-                    u32x2 pk;
-                    pk[0] = pack_bf16x2(v[0], v[1]);
-                    pk[1] = pack_bf16x2(v[2], v[3]);
-                    *reinterpret_cast<u32x2*>(stg + rl * PITCH + col * 2) = pk;
+            for (int i = 0; i < 2; ++i)
+                acc[2 * ha + i][hb] = Mfma<32>::run(fb[hb][ks], fa[i][ks], acc[2 * ha + i][hb]);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(0);
+        block_sync_lds();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // Bias (and LayerNorm g, b) of the wave's 64 columns, loaded into its staging area ahead of the epilogue.
+    uint16_t* const stg = smem + 2 * STAGE + wid * STG;
+    auto load_cols = [&](int n0) {
+        auto one = [&](const float* p, int at) {
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p) + n0 + wn * 64, 0, 256, 0x00020000);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)(stg + at * 128), 4, lane * 4, 0, 0, 0);
+        };
+        one(bias, 0);
+        if constexpr (kResLn<EPI>) {
+            one(res.g, 1);
+            one(res.b, 2);
+        }
+    };
+
+    int m0, n0, st = 0, landed = 0;  // landed: slabs from the current one on known to be in LDS
+    origin(tile, m0, n0);
+    load_cols(n0);
+    stream_tile();
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+        load_a(v * STAGE, 0);
+        load_b(v * STAGE, 0);
+        load_b(v * STAGE, 1);
+        load_a(v * STAGE, 1);
+        stream_next();
+    }
+    wait_vmcnt<12>();
+    block_sync_lds();
+    for (;;) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        if (wm == 1) block_sync_lds();
+        for (int k = 0; k < K; k += kBK) {
+            read_b(0);
+            read_a(0);
+            if (landed < 1) wait_vmcnt<10>();
+            multiply(0, 0);
+            read_b(1);
+            load_a(st, 0);
+            if (landed < 1) wait_vmcnt<10>();
+            multiply(0, 1);
+            read_a(1);
+            load_b(st, 0);
+            multiply(1, 1);
+            load_b(st, 1);
+            load_a(st, 1);
+            if (landed < 2) wait_vmcnt<12>();
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) pa[ks] ^= STAGE, pb[ks] ^= STAGE;
+            st ^= STAGE;
+            landed = landed > 0 ? landed - 1 : 0;
+            stream_next();
+            multiply(1, 0);
+        }
+        if (wm == 0) block_sync_lds();
+
+        // Epilogue: 32 rows x 128 bytes at a time through the wave's staging area, stored as whole lines.
+        const int rows = M - m0 < BM ? M - m0 : BM;
+        const uint32_t o_bytes = (static_cast<uint32_t>(rows) * N - n0) * EB;
+        const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+            static_cast<char*>(out) + (static_cast<size_t>(m0) * N + n0) * EB, 0, o_bytes, 0x00020000);
+        asm volatile("" ::: "memory");
+        f32x4 bv[2][4];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) bv[j][q] = *reinterpret_cast<const f32x4*>(stg + (j * 32 + 8 * q + 4 * kg) * 2);
+        const int ch = lane & 7, rr0 = lane >> 3;  // read-back: 16-byte chunk and row of 8
+        // Output offset of the lane's first row (rows past the end of the matrix are outside the resource) and of 8
+        // rows; formed anew for every tile, so that no row's offset is kept in a register through the k-loop.
+        uint32_t ro0 = (static_cast<uint32_t>(wm * 128 + rr0) * N + wn * 64) * EB + ch * 16, row8 = 8u * N * EB;
+        asm volatile("" : "+v"(ro0), "+s"(row8));
+        if constexpr (F32OUT) {
+            f32x4 gl[2], bl[2];
+            if constexpr (kResLn<EPI>) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    gl[j] = *reinterpret_cast<const f32x4*>(stg + 128 + (j * 32 + ch * 4) * 2);
+                    bl[j] = *reinterpret_cast<const f32x4*>(stg + 256 + (j * 32 + ch * 4) * 2);
                 }
             }
-        }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_wave_barrier();
-        asm volatile("" ::: "memory");
-        constexpr int NRR = 32 / RPR;  // read-back rows per lane per block row
-        if constexpr (F32OUT) {
-            // All residual vectors (and row statistics) of the block row are requested first.
-            f32x4 hv[NRR];
-            float2 sv[NRR];
+            const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<float*>(res.x) + static_cast<size_t>(m0) * N + n0, 0, o_bytes, 0x00020000);
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<float2*>(res.stats) + (kResLn<EPI> ? m0 : 0), 0, kResLn<EPI> ? rows * 8 : 0, 0x00020000);
+            f32x4 hv[2][4];
+            f32x2 sv[2][4];
+            // Residual rows (and statistics) of step b = 2 i + j, requested one step ahead.
+            uint32_t fo = ro0, so = ro0;
+            auto fetch = [&](int b) {
+                const int i = b >> 1, j = b & 1;
+                if (j == 1) fo -= 4 * row8;
 #pragma unroll
-            for (int rr = 0; rr < NRR; ++rr) {
-                const int m = m0 + wm * TM + i * MI + rr * RPR + lane / LPR;
-                const int mc = m < M ? m : M - 1;  // rows past the end load a valid row, store nothing
-                hv[rr] = *reinterpret_cast<const f32x4*>(res.x + static_cast<size_t>(mc) * N + nl);
-                if constexpr (kResLn<EPI>) sv[rr] = res.stats[mc];
-            }
+                for (int rr = 0; rr < 4; ++rr, fo += row8) {
+                    hv[b & 1][rr] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rx, fo, j * 128, 0));
+                    if constexpr (kResLn<EPI>)
+                        if (j == 0)
+                            sv[i & 1][rr] = __builtin_bit_cast(
+                                f32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, (wm * 128 + rr0 + i * 32 + rr * 8) * 8, 0, 0));
+                }
+            };
+            fetch(0);
 #pragma unroll
-            for (int rr = 0; rr < NRR; ++rr) {
-                const int row = rr * RPR + lane / LPR;
-                const int m = m0 + wm * TM + i * MI + row;
-                const u32x4 d = *reinterpret_cast<const u32x4*>(stg + row * PITCH + ch * 16);
-                if (m < M) {
-                    f32x4 h = hv[rr];
+            for (int b = 0; b < 8; ++b) {
+                const int i = b >> 1, j = b & 1;
+                if (b < 7) fetch(b + 1);
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    f32x4 v;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = acc[i][j][4 * q + r];
+                    *reinterpret_cast<f32x4*>(stg + rl * 64 + (((2 * q + kg) ^ swz(rl)) * 8)) = v + bv[j][q];
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr, so += row8) {
+                    const int row = rr * 8 + rr0;
+                    f32x4 h = hv[b & 1][rr];
                     if constexpr (kResLn<EPI>) {
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) h[c] = fmaf((h[c] - sv[rr].x) * sv[rr].y, gl[c], bl[c]);
+                        for (int c = 0; c < 4; ++c) h[c] = fmaf((h[c] - sv[i & 1][rr][0]) * sv[i & 1][rr][1], gl[j][c], bl[j][c]);
                     }
-                    const f32x4 v = __builtin_bit_cast(f32x4, d) + h;
-                    *reinterpret_cast<f32x4*>(static_cast<float*>(out) + static_cast<size_t>(m) * N + nl) = v;
+                    const f32x4 v = *reinterpret_cast<const f32x4*>(stg + row * 64 + ((ch ^ swz(row)) * 8)) + h;
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ro, so, j * 128, 0);
                 }
+                if (j == 0) so -= 4 * row8;
+                __builtin_amdgcn_sched_barrier(0);
             }
         } else {
 #pragma unroll
-            for (int rr = 0; rr < NRR; ++rr) {
-                const int row = rr * RPR + lane / LPR;
-                const int m = m0 + wm * TM + i * MI + row;
-                const u32x4 d = *reinterpret_cast<const u32x4*>(stg + row * PITCH + ch * 16);
-                if (m < M) __builtin_nontemporal_store(d, reinterpret_cast<u32x4*>(static_cast<uint16_t*>(out) + static_cast<size_t>(m) * N + nl));
+            for (int i = 0; i < 4; ++i) {
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        f32x4 v;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) v[r] = acc[i][j][4 * q + r];
+                        v += bv[j][q];
+                        if constexpr (EPI == ELIS_EPI_BIAS_GELU_BF16) {
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) v[c] = gelu_erf(v[c]);
+                        }
+                        u32x2 pk;
+                        pk[0] = pack_bf16x2(v[0], v[1]);
+                        pk[1] = pack_bf16x2(v[2], v[3]);
+                        *reinterpret_cast<u32x2*>(stg + rl * 64 + (((4 * j + q) ^ swz(rl)) * 8 + 4 * kg)) = pk;
+                    }
+                if (i == 0) wait_vmcnt<0>();  // the next tile's first two slabs are in LDS before the first store
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr, ro0 += row8) {
+                    const int row = rr * 8 + rr0;
+                    const u32x4 d = *reinterpret_cast<const u32x4*>(stg + row * 64 + ((ch ^ swz(row)) * 8));
+                    __builtin_amdgcn_raw_buffer_store_b128(d, ro, ro0, 0, 2);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_wave_barrier();
-        asm volatile("" ::: "memory");
+        tile += wgs;
+        if (tile >= t_end) break;
+        origin(tile, m0, n0);
+        load_cols(n0);
+        landed = 2;
+    }
+    wait_vmcnt<0>();  // the empty loads of the stream's end write LDS: none may outlive the work-group
+#endif
+}
+
+hipError_t launch_persist(const uint16_t* x, const uint16_t* w, const float* bias, Residual res, int m, int n, int k,
+                           int epi, void* out, hipStream_t st, int group_m) {
+    const int tiles = ((m + 255) / 256) * (n / 256), cus = device_cus();
+    const dim3 grid(tiles < cus ? tiles : cus), block(512);
+    auto go = [&](auto kernel) { return launch_kernel(kernel, grid, block, 0, st, x, w, bias, res, out, m, n, k, group_m); };
+    switch (epi) {
+        case ELIS_EPI_BIAS_BF16: return go(gemm_persist_kernel<ELIS_EPI_BIAS_BF16>);
+        case ELIS_EPI_BIAS_GELU_BF16: return go(gemm_persist_kernel<ELIS_EPI_BIAS_GELU_BF16>);
+        case ELIS_EPI_BIAS_RES_F32: return go(gemm_persist_kernel<ELIS_EPI_BIAS_RES_F32>);
+        case kEpiResLn: return go(gemm_persist_kernel<kEpiResLn>);
+        case kEpiResLnFfn2: return go(gemm_persist_kernel<kEpiResLnFfn2>);
+        default: return hipErrorInvalidValue;
     }
 }
 
 template <int BM, int BN, int WM, int WN, int MI, int OCC = 1, int S = 2>
 hipError_t launch_sched(const uint16_t* x, const uint16_t* w, const float* bias, Residual res, int m, int n,
                         int k, int epi, void* out, hipStream_t st, int group_m) {
-    const dim3 grid(((m + BM - 1) / BM) * (n / BN)), block(WM * WN * kWave);
-    switch (epi) {
-        case ELIS_EPI_BIAS_BF16:
-            ELIS_TRY(launch_kernel((gemm_sched_kernel<BM, BN, WM, WN, MI, ELIS_EPI_BIAS_BF16, OCC, S>), grid, block, 0, st, x, w, bias,
-                               res, out, m, n, k, group_m));
-            break;
-        case ELIS_EPI_BIAS_GELU_BF16:
-            ELIS_TRY(launch_kernel((gemm_sched_kernel<BM, BN, WM, WN, MI, ELIS_EPI_BIAS_GELU_BF16, OCC, S>), grid, block, 0, st, x, w,
-                               bias, res, out, m, n, k, group_m));
-            break;
-        case ELIS_EPI_BIAS_RES_F32:
-            ELIS_TRY(launch_kernel((gemm_sched_kernel<BM, BN, WM, WN, MI, ELIS_EPI_BIAS_RES_F32, OCC, S>), grid, block, 0, st, x, w,
-                               bias, res, out, m, n, k, group_m));
-            break;
-        case kEpiResLn:
-            ELIS_TRY(launch_kernel((gemm_sched_kernel<BM, BN, WM, WN, MI, kEpiResLn, OCC, S>), grid, block, 0, st, x, w, bias, res,
-                               out, m, n, k, group_m));
-            break;
-        case kEpiResLnFfn2:
-            ELIS_TRY(launch_kernel((gemm_sched_kernel<BM, BN, WM, WN, MI, kEpiResLnFfn2, OCC, S>), grid, block, 0, st, x, w, bias, res,
-                               out, m, n, k, group_m));
-            break;
-        default:
-            return hipErrorInvalidValue;
+    if constexpr (BM == 256 && BN == 256) {
+        // The persistent kernel needs two k-slabs and 32-bit offsets inside a tile's operands and output; other
+        // products of this configuration take 128 x 128 tiles (the same bits; at k = 64 also the faster tile:
+        // 3.8 against 5.6 us at 300 x 256).
+        if (k >= 2 * kBK && k <= (1 << 21) && n <= (1 << 20))
+            return launch_persist(x, w, bias, res, m, n, k, epi, out, st, group_m);
+        return launch_sched<128, 128, 2, 2, 32, 2>(x, w, bias, res, m, n, k, epi, out, st, group_m);
+    } else {
+        const dim3 grid(((m + BM - 1) / BM) * (n / BN)), block(WM * WN * kWave);
+        auto go = [&](auto kernel) { return launch_kernel(kernel, grid, block, 0, st, x, w, bias, res, out, m, n, k, group_m); };
+        switch (epi) {
+            case ELIS_EPI_BIAS_BF16: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, ELIS_EPI_BIAS_BF16, OCC, S>);
+            case ELIS_EPI_BIAS_GELU_BF16: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, ELIS_EPI_BIAS_GELU_BF16, OCC, S>);
+            case ELIS_EPI_BIAS_RES_F32: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, ELIS_EPI_BIAS_RES_F32, OCC, S>);
+            case kEpiResLn: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, kEpiResLn, OCC, S>);
+            case kEpiResLnFfn2: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, kEpiResLnFfn2, OCC, S>);
+            default: return hipErrorInvalidValue;
+        }
     }
-    return hipSuccess;
 }
 
 template <int BM, int BN, int WM, int WN, int MI>
@@ -578,52 +929,41 @@ int gemm_config_of_tile(int bm, int bn, int wgs_per_cu) {
     return -1;
 }
 
-// Compute units of the current device (the launch-time model below needs it). A device property,
-// looked up once per device; the cache is safe to read and fill from several host threads.
-int device_cus() {
-    static std::atomic<int> cus[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    int v = cus[dev].load(std::memory_order_relaxed);
-    if (v == 0) {
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
-        cus[dev].store(v, std::memory_order_relaxed);
-    }
-    return v;
-}
-
 namespace {
 
-// Launch-time model of the scheduled configurations, in microseconds on MI355X (256 CUs),
-// fitted to medians of repeated timings of the BERT-base and XLM-R-large encoder GEMMs
-// (K = 768 .. 4096, one to four rounds of tiles; all six configurations timed on one box).
+// Launch-time model of the tile configurations, in microseconds on MI355X (256 CUs), fitted to
+// medians of repeated timings over K = 768, 1024, 3072, 4096, the three epilogue kinds and ten
+// fills from a lone tile to four rounds, two sets of operands in turn (so that a product does not
+// find its weights and activations in the L2, as inside the encoder; a fit with everything L2-hot
+// had priced a lone two-stage 64 x 64 tile at half of what it takes there). Fit error: 2-8%, except the
+// lone tiles of the two-stage configurations (up to 26%, never the cheapest choice there).
 // A launch whose tiles fill R rounds of work-group slots (work-groups per CU x CUs), the last
 // one a fraction f full, takes part(f) for R = 1, else t1 + (R - 2) * beta + part(f)
 // - (t1 - beta) * f; part is piecewise linear through lat (a lone tile, f -> 0), th (f = 1/2)
-// and t1 (f = 1), beta is the cost of one more full round. Each quantity is a + s * K / 64: the slope per 64-deep k-slab is shared by the
-// epilogue kinds, the intercept is per kind (bf16, bf16 + GELU, fp32 + residual). The 64-row
-// tiles are priced only up to the four rounds they were timed on and are not offered past
-// that. Over every single and split plan of those shapes at 35 sizes (M = 1K .. 92K), timed
-// one by one, the plans it picks take 0.25-0.4% more time in total than the fastest ones
-// measured (two boxes).
+// and t1 (f = 1), beta is the cost of one more full round. Each quantity is a + s * K / 64: the
+// slope per 64-deep k-slab is shared by the epilogue kinds, the intercept is per kind (bf16,
+// bf16 + GELU, fp32 + residual). Full rounds of 256 x 256 tiles cost more per slab than a lone
+// tile (1.6-1.8 against 1.0 us): with every matrix core busy the clock falls to about 1.7 GHz.
+// The 64-row tiles are priced only up to the four rounds they were timed on and are not offered
+// past that.
 struct TileModel {
     int cfg, bm, bn, occ, max_rounds;  // max_rounds: 0 = any; else the fitted range
     float s[4];     // lat, th, t1, beta: slope per k-slab
     float a[3][4];  // intercept per epilogue kind
 };
 constexpr TileModel kTileModels[] = {
-    {21, 256, 256, 1, 0, {1.178f, 1.375f, 1.770f, 1.693f},
-     {{6.05f, 5.97f, 5.72f, 4.21f}, {11.77f, 11.79f, 11.15f, 10.12f}, {10.41f, 14.62f, 20.49f, 26.70f}}},
-    {32, 128, 128, 2, 0, {0.535f, 0.614f, 0.991f, 1.073f},
-     {{3.63f, 3.63f, 4.11f, 2.01f}, {5.24f, 6.32f, 7.50f, 4.91f}, {4.94f, 9.43f, 12.78f, 12.17f}}},
-    {33, 64, 128, 2, 4, {0.363f, 0.556f, 0.594f, 0.754f},
-     {{2.94f, 2.37f, 3.95f, 0.42f}, {3.69f, 1.94f, 4.59f, 1.10f}, {3.45f, 3.46f, 8.15f, 3.02f}}},
-    {34, 64, 128, 1, 4, {0.340f, 0.395f, 0.436f, 0.353f},
-     {{3.49f, 2.78f, 2.74f, 2.45f}, {4.11f, 3.68f, 3.67f, 3.50f}, {4.17f, 3.89f, 5.00f, 4.40f}}},
-    {35, 64, 64, 4, 4, {0.227f, 0.481f, 0.757f, 0.844f},
-     {{2.78f, 1.95f, 3.73f, -0.05f}, {3.11f, 1.74f, 4.15f, 0.50f}, {3.24f, 3.77f, 6.41f, 1.22f}}},
-    {36, 64, 64, 2, 4, {0.251f, 0.259f, 0.411f, 0.393f},
-     {{2.47f, 2.85f, 3.10f, 1.40f}, {3.23f, 3.40f, 3.12f, 1.82f}, {2.97f, 4.12f, 4.86f, 2.60f}}},
+    {21, 256, 256, 1, 0, {1.009f, 1.150f, 1.614f, 1.765f},
+     {{5.05f, 6.28f, 8.18f, 1.99f}, {9.49f, 9.77f, 9.86f, 5.44f}, {8.25f, 14.11f, 26.44f, 17.76f}}},
+    {32, 128, 128, 2, 0, {0.583f, 0.648f, 1.009f, 1.180f},
+     {{2.60f, 3.33f, 3.75f, 0.91f}, {4.27f, 4.83f, 5.72f, 2.55f}, {4.22f, 7.72f, 11.39f, 11.14f}}},
+    {33, 64, 128, 2, 4, {0.354f, 0.514f, 0.605f, 0.770f},
+     {{2.62f, 2.92f, 3.73f, -0.52f}, {4.32f, 3.71f, 4.22f, 0.59f}, {4.06f, 5.05f, 6.94f, 4.36f}}},
+    {34, 64, 128, 1, 4, {0.321f, 0.333f, 0.367f, 0.372f},
+     {{2.86f, 3.07f, 3.44f, 1.58f}, {3.87f, 3.71f, 4.02f, 2.14f}, {3.56f, 4.26f, 5.65f, 3.58f}}},
+    {35, 64, 64, 4, 4, {0.305f, 0.456f, 0.771f, 0.869f},
+     {{1.42f, 2.95f, 3.70f, -1.34f}, {2.71f, 3.17f, 3.50f, -0.58f}, {2.95f, 4.49f, 4.95f, 3.62f}}},
+    {36, 64, 64, 2, 4, {0.218f, 0.237f, 0.377f, 0.380f},
+     {{2.83f, 2.93f, 3.18f, 1.29f}, {3.29f, 3.07f, 3.61f, 1.50f}, {3.35f, 3.86f, 4.78f, 2.16f}}},
 };
 constexpr float kSecondLaunchUs = 1.0f;  // dispatch cost of the remainder launch
 

@@ -1,0 +1,107 @@
+"""The persistent 256 x 256 product kernel: a CPU mirror of its addresses, and its bits on the GPU.
+
+The mirror re-evaluates, over all work-groups, waves and lanes, which tiles a work-group walks, what
+the direct loads fetch into which place of LDS, what the fragment reads take from there, and which
+output bytes the epilogue stores (rows past the end must fall outside the buffer resource). On the
+GPU every size is compared bit for bit with 128 x 128 tiles: one tile and several per work-group,
+ragged rows, odd and even slab counts, and the depths the kernel hands on (k = 64).
+"""
+import numpy as np
+import pytest
+
+from paper_2505_09142_amd import _elis as E
+
+GROUP_M, CUS = 8, 256
+
+
+def tiles_of(bid, grid, tiles):
+    """Tile indices of one work-group: its XCD's contiguous range, dealt out to the XCD's work-groups."""
+    xcd, per, rem = bid & 7, tiles >> 3, tiles & 7
+    count = per + (xcd < rem)
+    end = xcd * per + min(xcd, rem) + count
+    return list(range(end - count + (bid >> 3), end, (grid - xcd + 7) >> 3))
+
+
+@pytest.mark.parametrize("tiles", [1, 2, 7, 8, 9, 63, 255, 256, 257, 282, 1092, 4368])
+def test_every_tile_is_walked_once(tiles):
+    grid = min(tiles, CUS)
+    walked = [tiles_of(b, grid, tiles) for b in range(grid)]
+    assert all(walked)  # a work-group's first tile always exists
+    assert sorted(sum(walked, [])) == list(range(tiles))
+
+
+def swz(row):
+    return (row >> 1) & 7
+
+
+def test_loads_and_fragment_reads_agree():
+    """Each half-slab is filled once, and a fragment read of (row, k) sees that element of the tile."""
+    lane = np.arange(64)
+    for operand, row_of in (("a", lambda h, r: (r >> 6) * 128 + h * 64 + (r & 63)), ("b", lambda h, r: (r >> 5) * 64 + h * 32 + (r & 31))):
+        for h in (0, 1):
+            lds = np.full((128 * 8, 2), -1)  # 16-byte unit of the half-slab -> (tile row, logical chunk)
+            for w in range(8):
+                for i in (0, 1):
+                    r = w * 16 + i * 8 + (lane >> 3)
+                    unit = (w * 16 + i * 8) * 8 + lane  # the load writes lane i's 16 bytes at base + 16 i
+                    assert np.all(lds[unit] == -1)
+                    lds[unit, 0], lds[unit, 1] = row_of(h, r), (lane & 7) ^ swz(r)
+            assert np.all(lds >= 0) and len({tuple(x) for x in lds}) == 128 * 8
+            for w in range(8):  # wave block: rows 128 (w / 4) + 64 h + 32 i, columns 64 (w % 4) + 32 h
+                for i in range(2 if operand == "a" else 1):
+                    for ks in range(4):
+                        rl, kg = lane & 31, lane >> 5
+                        first = (w >> 2) * 64 + i * 32 if operand == "a" else (w & 3) * 32
+                        unit = (first + rl) * 8 + ((ks * 2 + kg) ^ swz(rl))
+                        want = (w >> 2) * 128 + h * 64 + i * 32 + rl if operand == "a" else (w & 3) * 64 + h * 32 + rl
+                        assert np.array_equal(lds[unit, 0], want) and np.array_equal(lds[unit, 1], ks * 2 + kg)
+
+
+@pytest.mark.parametrize("M", [1, 31, 128, 255, 256, 257, 511])
+@pytest.mark.parametrize("f32", [False, True])
+def test_stores_cover_the_output_once(M, f32):
+    N, eb = 512, 4 if f32 else 2
+    lane = np.arange(64)
+    ch, rr0 = lane & 7, lane >> 3
+    out = np.zeros((M * N * eb) // 16, int)
+    for m0 in range(0, M, 256):
+        rows = min(256, M - m0)
+        for n0 in range(0, N, 256):
+            size, base = (rows * N - n0) * eb, (m0 * N + n0) * eb
+            for w in range(8):
+                wm, wn = w >> 2, w & 3
+                for i in range(4):
+                    for j in range(2 if f32 else 1):
+                        for rr in range(4):
+                            row = wm * 128 + i * 32 + rr * 8 + rr0
+                            off = (row * N + wn * 64) * eb + ch * 16
+                            keep = off < size  # the resource drops the others, with and without the scalar offset
+                            assert np.array_equal(keep, off < size - j * 128) and np.array_equal(keep, row < rows)
+                            np.add.at(out, (base + off[keep] + j * 128) // 16, 1)
+    assert np.all(out == 1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("epi", [E.ELIS_EPI_BIAS_BF16, E.ELIS_EPI_BIAS_GELU_BF16, E.ELIS_EPI_BIAS_RES_F32])
+@pytest.mark.parametrize("m,n,k", [(1, 256, 128), (257, 256, 64), (300, 512, 192), (513, 768, 256), (65793, 256, 128),
+                                   (25000, 768, 320)])
+def test_same_bits_as_small_tiles(m, n, k, epi):
+    import torch
+    from tests.gpu_util import note, ok, stream
+    note(f"persistent product m={m} n={n} k={k} epi={epi}")
+    gen = torch.Generator(device="cuda").manual_seed(m + n + k)
+    x = torch.randn((m, k), generator=gen, device="cuda").to(torch.bfloat16)
+    w = (0.05 * torch.randn((n, k), generator=gen, device="cuda")).to(torch.bfloat16)
+    bias = torch.randn(n, generator=gen, device="cuda")
+    f32 = epi == E.ELIS_EPI_BIAS_RES_F32
+    res = torch.randn((m, n), generator=gen, device="cuda") if f32 else None
+    guard = 4096  # elements past the output that must stay as they are
+    outs = []
+    for tile in ((256, 256, 1), (128, 128, 2)):
+        out = torch.full((m * n + guard,), 7.0, dtype=torch.float32 if f32 else torch.bfloat16, device="cuda")
+        ok(E.elis_linear_with_plan(x.data_ptr(), w.data_ptr(), bias.data_ptr(), res.data_ptr() if f32 else None, m, n, k, epi,
+                                   (*tile, m, 0, 0, 0), out.data_ptr(), stream()))
+        torch.cuda.synchronize()
+        assert bool((out[m * n:] == 7.0).all())
+        outs.append(out[:m * n].view(torch.int32 if f32 else torch.int16))
+    assert torch.equal(outs[0], outs[1])
