@@ -147,9 +147,8 @@ int32_t elis_select_max_n(void);
 
 /*
  * Largest min(batch_cap, n) accepted for n jobs (0 if n is invalid): unbounded
- * (INT32_MAX) for n <= 8192, where one work-group sorts every job; 8192 above,
- * where the chosen jobs are sorted by one work-group after a device-wide radix
- * selection.
+ * (INT32_MAX) for n <= 8192, where every job is ranked; 8192 above, where the
+ * chosen jobs are ranked after a device-wide selection.
  */
 int32_t elis_select_max_batch_cap(int32_t n);
 

@@ -118,6 +118,15 @@ struct JobTable {
     int32_t* ring;     // [J][max_pos - 1]
     int max_jobs, max_pos;
 };
+// Select key of candidate i. With `wait` (seconds each job has waited since it last ran, fp32), it is
+// aged: fl32(key - aging * wait) evaluated in fp64 from the fp32 operands, with the product and the
+// difference each rounded once (no fused multiply-add), so the rank order is reproducible exactly in
+// any IEEE fp64 arithmetic.
+__device__ __forceinline__ float jobs_key(float pred, const float* wait, float aging, int i) {
+    if (!wait) return pred;
+    return __double2float_rn(__dsub_rn(static_cast<double>(pred),
+                                       __dmul_rn(static_cast<double>(aging), static_cast<double>(wait[i]))));
+}
 size_t jobs_table_bytes(int max_jobs, int max_pos);
 JobTable jobs_table(void* base, int max_jobs, int max_pos);
 hipError_t launch_jobs_init(JobTable t, hipStream_t st);
@@ -128,6 +137,12 @@ hipError_t launch_jobs_pack(JobTable t, const int32_t* slots, int n, int total, 
                             int32_t* cu, hipStream_t st);
 hipError_t launch_jobs_store_pred(JobTable t, const int32_t* slots, const float* pred, int n, hipStream_t st);
 size_t jobs_select_workspace_bytes(int max_active);
+// Keys and arrivals of the jobs in slots[0..a), and the chosen positions' slots (count read on the device).
+hipError_t launch_jobs_gather(JobTable t, const int32_t* slots, const float* wait, float aging, int a, float* pred,
+                              int64_t* arrival, hipStream_t st);
+hipError_t launch_jobs_map(const int32_t* slots, const int32_t* idx, const int32_t* count, int cap, int32_t* out,
+                           hipStream_t st);
+// select.hip
 // wait: null, or fp32 [a] seconds waited, aging the keys by `aging` tokens per second.
 hipError_t launch_jobs_select(JobTable t, const int32_t* slots, const float* wait, float aging, int a, int k,
                               int32_t* out_slots, int32_t* out_count, void* workspace, hipStream_t st);

@@ -6,12 +6,11 @@
 //   * the float is mapped to an unsigned integer whose order is the float
 //     order, with -0 folded onto +0 and every NaN mapped to the maximum (after
 //     +inf), so the comparison is exact integer work with no rounding;
-//   * n <= 1024: one work-group ranks every key by counting the keys below it
-//     (keys in LDS, read as broadcasts), and the job of rank r < k lands in
-//     out_idx[r];
-//   * 1024 < n <= 8192: one work-group bitonic-sorts the keys in LDS (padded
-//     to a power of two with +max sentinels) and writes the first k;
-//   * larger n (k <= 8192): radix selection over the whole device, most
+//   * n <= 8192: every work-group ranks a few jobs by counting the keys below
+//     theirs (all keys in LDS), and the job of rank r < k lands in out_idx[r];
+//   * larger n (k <= 8192), where the smallest jobs of some groups bound the number of
+//     candidates (see "group minima"): three launches;
+//   * else radix selection over the whole device, most
 //     significant digit first. Three counting passes over the float keys
 //     (11, 11, 10 bits) fix the key P of the k-th job: in every pass each
 //     work-group histograms its own contiguous chunk of jobs (those matching
@@ -20,12 +19,12 @@
 //     k-th job. A scatter pass then lists, per chunk and in index order, the
 //     jobs with key < P and the ties (key == P). Nothing in these passes is a
 //     same-address global atomic (those serialise at tens of ns apiece across
-//     the XCDs). A single work-group finishes: it takes the needed number of
+//     the XCDs). A single work-group takes the needed number of
 //     ties by (arrival, index) - an LDS sort when there are at most 8192 of
 //     them, otherwise a radix selection of its own over the 96-bit
-//     (arrival, index) keys - and sorts the k chosen jobs by the full key.
-//     The pred array is read four times (16 bytes per job); arrivals are read
-//     for ties only.
+//     (arrival, index) keys - and lists the k chosen jobs, which the ranking
+//     kernel puts in order. The pred array is read four times (16 bytes per
+//     job); arrivals are read for ties only.
 #include <limits.h>
 
 #include <mutex>
@@ -37,8 +36,8 @@ namespace elis {
 namespace {
 
 constexpr int kThreads = 1024;
-constexpr int kRankMaxN = 1024;
-constexpr int kSortMaxN = 8192;
+constexpr int kRankMaxN = 8192;  // most jobs of one ranking launch
+constexpr int kSortMaxN = 8192;  // most jobs of one LDS sort
 
 __device__ __forceinline__ uint32_t order_key(float f) {
     uint32_t u = __float_as_uint(f);
@@ -53,89 +52,126 @@ __device__ __forceinline__ bool key_less(uint32_t ka, int64_t aa, int ia, uint32
     return ia < ib;
 }
 
-__global__ __launch_bounds__(kThreads) void select_rank_kernel(const float* __restrict__ pred,
-                                                               const int64_t* __restrict__ arrival, int n, int k,
-                                                               int32_t* __restrict__ out_idx,
+// Where the ranking kernel gets job i's key and arrival from, and what it writes for a chosen job.
+struct PlainJobs {
+    const float* pred;
+    const int64_t* arrival;
+    const int32_t* slots;  // null: write the index, else slots[index]
+    __device__ float key(int i) const { return pred[i]; }
+    __device__ int64_t arrived(int i) const { return arrival[i]; }
+    __device__ bool before(int i, int j) const { return i < j; }  // the lower index, between equal arrivals
+    __device__ int32_t chosen(int i) const { return slots ? slots[i] : i; }
+    __device__ void check(int) const {}
+};
+
+// The jobs of a table, their keys aged when wait is given (jobs_key in kernels.h).
+struct TableJobs {
+    JobTable t;
+    const int32_t* slots;
+    const float* wait;
+    float aging;
+    __device__ bool ok(int32_t s) const { return s >= 0 && s < t.max_jobs; }
+    __device__ float key(int i) const {
+        const int32_t s = slots[i];
+        return ok(s) ? jobs_key(t.pred[s], wait, aging, i) : __int_as_float(0x7fc00000);
+    }
+    __device__ int64_t arrived(int i) const {
+        const int32_t s = slots[i];
+        return ok(s) ? t.arrival[s] : 0;
+    }
+    __device__ bool before(int i, int j) const { return i < j; }
+    __device__ int32_t chosen(int i) const { return slots[i]; }
+    __device__ void check(int i) const {
+        if (!ok(slots[i])) atomicOr(t.status, ELIS_DEV_BAD_SLOT);
+    }
+};
+
+// Ranks a work-group's J jobs among all n <= 8192 and writes those of rank below k. Every
+// work-group holds all n float keys in LDS; a thread counts, for one of the J jobs, the smaller
+// keys of its slice of them (16 bytes per LDS read, two instructions per key). Only a job with
+// fewer than k smaller keys can be chosen: a wave looks through the keys equal to its own and
+// ranks those by (arrival, index). n * n / 64 lane steps, spread over up to 256 CUs.
+// Bound by launch and load latency up to about 2,000 jobs, then by the counting. It replaces one
+// work-group that ranked up to 1,024 jobs by full comparisons and sorted up to 8,192 in LDS:
+// 256 jobs 12 -> 3.8 us, 1,024 jobs 64 -> 4, 4,096 jobs 74 -> 5.5, 8,192 jobs 151 -> 11 (k = 64).
+template <int J, class Jobs>
+__global__ __launch_bounds__(kThreads) void select_rank_kernel(Jobs jobs, int n, int k, int32_t* __restrict__ out_idx,
                                                                int32_t* __restrict__ out_count,
                                                                uint32_t* __restrict__ status) {
-    __shared__ uint32_t sk[kRankMaxN];
-    __shared__ int64_t sa[kRankMaxN];
-    const int i = threadIdx.x;
-    if (i < n) {
-        sk[i] = order_key(pred[i]);
-        sa[i] = arrival[i];
+    __shared__ __attribute__((aligned(16))) uint32_t sk[kRankMaxN];
+    __shared__ int part[kThreads / kWave][J];
+    constexpr int PER = J == 16 ? 4 : 8;  // keys a thread loads, all in flight together: n <= 1024 PER
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    const int n4 = (n + 3) / 4, i0 = blockIdx.x * J;
+    float f[PER];
+#pragma unroll
+    for (int c = 0; c < PER; ++c) f[c] = tid + c * kThreads < n ? jobs.key(tid + c * kThreads) : 0.f;
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+        const int i = tid + c * kThreads;
+        if (i < 4 * n4) sk[i] = i < n ? order_key(f[c]) : 0xffffffffu;  // padding is below nothing
     }
     __syncthreads();
-    if (i < n) {
-        const uint32_t ki = sk[i];
-        const int64_t ai = sa[i];
-        // rank = number of jobs ordered before job i (key, then arrival, then index), counted
-        // without branches so the LDS reads of consecutive j overlap
-        int rank = 0;
-#pragma unroll 8
-        for (int j = 0; j < n; ++j) {
-            const uint32_t kj = sk[j];
-            const int64_t aj = sa[j];
-            rank += static_cast<int>((kj < ki) | ((kj == ki) & ((aj < ai) | ((aj == ai) & (j < i)))));
+    const uint4* s4 = reinterpret_cast<const uint4*>(sk);
+    {
+        const int i = i0 + (tid & (J - 1));
+        const uint32_t ki = sk[i < n ? i : 0];
+        int below = 0;
+#pragma unroll 4
+        for (int q = tid / J; q < n4; q += kThreads / J) {
+            const uint4 v = s4[q];
+            below += static_cast<int>(v.x < ki) + static_cast<int>(v.y < ki) + static_cast<int>(v.z < ki) +
+                     static_cast<int>(v.w < ki);
         }
-        if (rank < k) out_idx[rank] = i;
+#pragma unroll
+        for (int o = J; o < kWave; o <<= 1) below += __shfl_xor(below, o, kWave);
+        if (lane < J) part[wid][lane] = below;
     }
-    if (i == 0) {
+    __syncthreads();
+    for (int r = wid; r < J; r += kThreads / kWave) {  // one wave per job; all but the tie count is uniform over it
+        const int i = i0 + r;
+        if (i >= n) break;
+        if (lane == 0) jobs.check(i);
+        int rank = 0;
+#pragma unroll
+        for (int w = 0; w < kThreads / kWave; ++w) rank += part[w][r];
+        if (rank >= k) continue;
+        const uint32_t ki = sk[i];
+        int ties = 0;
+#pragma unroll 4
+        for (int q = lane; q < n4; q += kWave) {
+            const uint4 v = s4[q];
+            const uint32_t e[4] = {v.x, v.y, v.z, v.w};
+            if ((v.x == ki) | (v.y == ki) | (v.z == ki) | (v.w == ki)) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int j = 4 * q + c;
+                    if (e[c] == ki && j != i && j < n) {
+                        const int64_t ai = jobs.arrived(i), aj = jobs.arrived(j);
+                        ties += static_cast<int>(aj != ai ? aj < ai : jobs.before(j, i));
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) ties += __shfl_xor(ties, o, kWave);
+        rank += ties;
+        if (lane == 0 && rank < k) out_idx[rank] = jobs.chosen(i);
+    }
+    if (blockIdx.x == 0 && tid == 0) {
         *out_count = k < n ? k : n;
-        *status = 0u;
+        if (status) *status = 0u;
     }
 }
 
-__global__ __launch_bounds__(kThreads) void select_sort_kernel(const float* __restrict__ pred,
-                                                               const int64_t* __restrict__ arrival, int n, int k,
-                                                               int32_t* __restrict__ out_idx,
-                                                               int32_t* __restrict__ out_count,
-                                                               uint32_t* __restrict__ status) {
-    __shared__ uint32_t sk[kSortMaxN];
-    __shared__ int32_t si[kSortMaxN];
-    __shared__ int64_t sa[kSortMaxN];
-    int P = 1;
-    while (P < n) P <<= 1;
-    for (int i = threadIdx.x; i < P; i += kThreads) {
-        if (i < n) {
-            sk[i] = order_key(pred[i]);
-            sa[i] = arrival[i];
-            si[i] = i;
-        } else {
-            sk[i] = 0xffffffffu;
-            sa[i] = LLONG_MAX;
-            si[i] = INT_MAX;
-        }
-    }
-    __syncthreads();
-    for (int size = 2; size <= P; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int t = threadIdx.x; t < (P >> 1); t += kThreads) {
-                const int lo = 2 * t - (t & (stride - 1));
-                const int hi = lo + stride;
-                const bool up = (lo & size) == 0;
-                const bool hi_first = key_less(sk[hi], sa[hi], si[hi], sk[lo], sa[lo], si[lo]);
-                if (hi_first == up) {
-                    const uint32_t tk = sk[lo];
-                    sk[lo] = sk[hi];
-                    sk[hi] = tk;
-                    const int64_t ta = sa[lo];
-                    sa[lo] = sa[hi];
-                    sa[hi] = ta;
-                    const int32_t ti = si[lo];
-                    si[lo] = si[hi];
-                    si[hi] = ti;
-                }
-            }
-            __syncthreads();
-        }
-    }
-    const int m = k < n ? k : n;
-    for (int r = threadIdx.x; r < m; r += kThreads) out_idx[r] = si[r];
-    if (threadIdx.x == 0) {
-        *out_count = m;
-        *status = 0u;
-    }
+template <class Jobs>
+hipError_t launch_rank(const Jobs& jobs, int n, int k, int32_t* out_idx, int32_t* out_count, uint32_t* status,
+                       hipStream_t st) {
+    // 16 jobs per work-group keep all 256 CUs busy up to 4,096 jobs; above, 32 halve the keys read per job.
+    const dim3 block(kThreads);
+    if (n <= 4096)
+        return launch_kernel(select_rank_kernel<16, Jobs>, dim3((n + 15) / 16), block, 0, st, jobs, n, k, out_idx, out_count, status);
+    return launch_kernel(select_rank_kernel<32, Jobs>, dim3((n + 31) / 32), block, 0, st, jobs, n, k, out_idx, out_count, status);
 }
 
 // ------------------------------------------------------------------------------ large n
@@ -163,7 +199,7 @@ struct LargeWs {
     uint32_t* counts;   // [groups][2] jobs chosen / tied, per work-group
     int32_t* chosen;    // [groups][kSortMaxN] chosen indices, per work-group
     int32_t* ties;      // [n] tied indices, each work-group at the start of its own chunk
-    int32_t* picked;    // [kSortMaxN] ties taken by (arrival, index)
+    int32_t* picked;    // [kSortMaxN] ties taken by (arrival, index), then the other chosen jobs
     int chunk;          // jobs per work-group
     int groups;
 };
@@ -441,10 +477,8 @@ __device__ __forceinline__ int find_group(const uint32_t* offs, int groups, uint
     return lo;
 }
 
-// Final work-group: choose the needed ties by (arrival, index), then sort the k chosen jobs.
-__global__ __launch_bounds__(kThreads) void select_final_kernel(const float* __restrict__ pred,
-                                                                const int64_t* __restrict__ arrival, int k, LargeWs ws,
-                                                                int32_t* __restrict__ out_idx) {
+// One work-group: choose the needed ties by (arrival, index), then list the k chosen jobs.
+__global__ __launch_bounds__(kThreads) void select_ties_kernel(const int64_t* __restrict__ arrival, LargeWs ws) {
     __shared__ uint32_t sk[kSortMaxN];
     __shared__ int64_t sa[kSortMaxN];
     __shared__ int32_t si[kSortMaxN];
@@ -568,29 +602,332 @@ __global__ __launch_bounds__(kThreads) void select_final_kernel(const float* __r
             __syncthreads();
         }
     }
-    // The k chosen jobs: nchosen from the scatter plus npicked ties; sort by the full key.
-    const int P = pow2_at_least(k);
-    for (int r = threadIdx.x; r < P; r += kThreads) {
-        if (r < k) {
-            int32_t j;
-            if (r < static_cast<int>(nchosen)) {
-                const int g = find_group(offc, groups, static_cast<uint32_t>(r));
-                j = ws.chosen[static_cast<size_t>(g) * kSortMaxN + (r - static_cast<int>(offc[g]))];
-            } else {
-                j = ws.picked[r - static_cast<int>(nchosen)];
+    // The jobs chosen by the scatter behind the ties: one list of k, which the ranking kernel orders.
+    for (int r = threadIdx.x; r < static_cast<int>(nchosen); r += kThreads) {
+        const int g = find_group(offc, groups, static_cast<uint32_t>(r));
+        ws.picked[npicked + r] = ws.chosen[static_cast<size_t>(g) * kSortMaxN + (r - static_cast<int>(offc[g]))];
+    }
+}
+
+// Jobs named by a list of indices, for the ranking kernel.
+struct ListedJobs {
+    const float* pred;
+    const int64_t* arrival;
+    const int32_t* list;
+    __device__ float key(int i) const { return pred[list[i]]; }
+    __device__ int64_t arrived(int i) const { return arrival[list[i]]; }
+    __device__ bool before(int i, int j) const { return list[i] < list[j]; }
+    __device__ int32_t chosen(int i) const { return list[i]; }
+    __device__ void check(int) const {}
+};
+
+// ------------------------------------------------------------------------------ group minima
+// Selection in three launches where few jobs can come into question, from the smallest job (in the
+// full order) of each of up to 4,096 groups: the k-th smallest of these minima bounds the k-th job
+// from above, and only the k groups whose minimum it reaches hold candidates. At most k groups of
+// jobs are candidates, whatever the data; on data without structure hardly more than k jobs are.
+//   minima     every group's smallest job;
+//   filter     every work-group finds the k-th smallest minimum by itself (block_kth, per 32-bit word
+//              of the full key) and lists its own jobs up to it;
+//   rank list  the candidates are ranked as in select_rank_kernel.
+// The radix path takes nine launches and four reads of the keys: 45 us at 2^20 jobs, k = 64, this one
+// 20 (4.5 + 9 + 6: launches, load latency and the barriers of the search; the keys are 4 MB).
+constexpr int kMinWgs = 256, kMinGroups = 16;  // work-groups, and groups of each
+constexpr int kCandidates = 32768;             // most candidates: their keys are ranked out of LDS
+constexpr int kMinMaxN = 1 << 21;
+constexpr int kMinAllN = 12288;                // every job may be a candidate up to here
+
+struct MinimaWs {
+    uint32_t* key;    // [kMinWgs * kMinGroups] minima: ordered key and index (no job: the largest key, index -1)
+    int32_t* idx;
+    int32_t* count;   // [kMinWgs] candidates of each work-group
+    uint32_t* ckey;   // [kMinWgs][cap] their keys and indices
+    int32_t* cidx;
+    int lanes;        // lanes (of 4 jobs a sweep) per group
+    int sweeps;       // 1024-thread sweeps of a work-group's jobs
+    int cap;          // jobs of a work-group, rounded up
+};
+
+// Quad u of work-group b: segments of 16 jobs are dealt out in turn, so that jobs in order of their
+// keys spread over all work-groups and groups.
+__device__ __forceinline__ int quad_first(int b, int u) { return ((u >> 2) * kMinWgs + b) * 16 + (u & 3) * 4; }
+
+__device__ __forceinline__ bool job_less(uint32_t ka, int ia, uint32_t kb, int ib, const int64_t* arrival) {
+    if (ia < 0 || ib < 0) return ib < 0 && ia >= 0;
+    if (ka != kb) return ka < kb;
+    const int64_t aa = arrival[ia], ab = arrival[ib];
+    return aa != ab ? aa < ab : ia < ib;
+}
+
+__global__ __launch_bounds__(kThreads) void select_minima_kernel(const float* __restrict__ pred,
+                                                                 const int64_t* __restrict__ arrival, int n,
+                                                                 MinimaWs ws) {
+    const bool vec = (reinterpret_cast<uintptr_t>(pred) & 15u) == 0;
+    uint32_t bk = 0xffffffffu;
+    int bi = -1;
+    for (int s = 0; s < ws.sweeps; ++s) {
+        const int i0 = quad_first(blockIdx.x, s * kThreads + threadIdx.x);
+        if (i0 >= n) continue;
+        float v[4];
+        load4(pred, i0, n, vec, v);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t key = order_key(v[c]);
+            if (i0 + c < n && job_less(key, i0 + c, bk, bi, arrival)) bk = key, bi = i0 + c;
+        }
+    }
+    for (int o = 1; o < ws.lanes; o <<= 1) {
+        const uint32_t ok = __shfl_xor(bk, o, kWave);
+        const int oi = __shfl_xor(bi, o, kWave);
+        if (job_less(ok, oi, bk, bi, arrival)) bk = ok, bi = oi;
+    }
+    const int g = static_cast<int>(threadIdx.x) / ws.lanes;
+    if (threadIdx.x % ws.lanes == 0 && g < kMinGroups) {
+        ws.key[blockIdx.x * kMinGroups + g] = bk;
+        ws.idx[blockIdx.x * kMinGroups + g] = bi;
+    }
+}
+
+// Scratch of block_kth.
+struct KthScratch {
+    uint32_t range[2][kThreads / kWave];
+    int wave[kThreads / kWave];
+    int bin[kThreads];
+    int found, below;
+};
+
+// The smallest v such that at least need of the work-group's active values are <= v; need becomes its
+// rank among the values equal to v, active their number, and only those stay active. The range of the
+// active values (small arrival numbers and one round's predictions span far fewer than 32 bits) is cut to
+// one of 1,024 equal parts at a time: two or three counting rounds in LDS (a binary search, two barriers
+// for each of its 24 steps, took 13 us for 4,096 minima; this 3).
+template <int PER>
+__device__ __forceinline__ uint32_t block_kth(const uint32_t (&v)[PER], bool (&act)[PER], int& need, int& active,
+                                              KthScratch& sh) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        lo = act[q] && v[q] < lo ? v[q] : lo;
+        hi = act[q] && v[q] > hi ? v[q] : hi;
+    }
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t a = __shfl_xor(lo, o, kWave), b = __shfl_xor(hi, o, kWave);
+        lo = a < lo ? a : lo;
+        hi = b > hi ? b : hi;
+    }
+    __syncthreads();  // the scratch may still be read from the last call
+    if (lane == 0) sh.range[0][wid] = lo, sh.range[1][wid] = hi;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kThreads / kWave; ++w) {
+        lo = sh.range[0][w] < lo ? sh.range[0][w] : lo;
+        hi = sh.range[1][w] > hi ? sh.range[1][w] : hi;
+    }
+    for (;;) {  // uniform: 32 bits are gone after four rounds
+        const int bits = hi > lo ? 32 - __builtin_clz(hi - lo) : 0, shift = bits > 10 ? bits - 10 : 0;
+        sh.bin[tid] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (act[q]) atomicAdd(&sh.bin[(v[q] - lo) >> shift], 1);
+        __syncthreads();
+        const int mine = sh.bin[tid];
+        int incl = mine;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int u = __shfl_up(incl, o, kWave);
+            if (lane >= o) incl += u;
+        }
+        if (lane == kWave - 1) sh.wave[wid] = incl;
+        __syncthreads();
+        for (int w = 0; w < wid; ++w) incl += sh.wave[w];
+        if (incl - mine < need && need <= incl) {  // one thread: the bin that holds the need-th value
+            sh.found = tid;
+            sh.below = incl - mine;
+        }
+        __syncthreads();
+        const uint32_t bin = static_cast<uint32_t>(sh.found);
+        need -= sh.below;
+        active = sh.bin[bin];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) act[q] = act[q] && ((v[q] - lo) >> shift) == bin;
+        lo += bin << shift;
+        if (shift == 0) return lo;
+        const uint32_t top = lo + ((1u << shift) - 1u);
+        hi = top < hi ? top : hi;
+        __syncthreads();  // bins are cleared again
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void select_filter_kernel(const float* __restrict__ pred,
+                                                                 const int64_t* __restrict__ arrival, int n, int k,
+                                                                 MinimaWs ws) {
+    __shared__ KthScratch sh;
+    __shared__ int cnt[kThreads / kWave];
+    __shared__ int listed;
+    if (threadIdx.x == 0) listed = 0;
+    constexpr int PER = kMinWgs * kMinGroups / kThreads, kSweeps = kMinMaxN / (4 * kThreads * kMinWgs);
+    const bool vec = (reinterpret_cast<uintptr_t>(pred) & 15u) == 0;
+    float v[kSweeps][4];  // this thread's jobs, requested before the search
+#pragma unroll
+    for (int s = 0; s < kSweeps; ++s) load4(pred, quad_first(blockIdx.x, s * kThreads + threadIdx.x), s < ws.sweeps ? n : 0, vec, v[s]);
+    uint32_t mk[PER];
+    int mi[PER];
+    bool act[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        mk[q] = ws.key[q * kThreads + threadIdx.x];
+        mi[q] = ws.idx[q * kThreads + threadIdx.x];
+        act[q] = mi[q] >= 0;
+    }
+    int need = k, active = 0;
+    // Bound: jobs below (key, arrival, index), the last two only when some of the minima with this key are above it.
+    uint32_t bound_k = 0xffffffffu;
+    uint64_t bound_a = ~0ull;
+    int bound_i = INT_MAX;
+    bool whole = true;  // every job with the bound's key is a candidate
+    int jobs = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) jobs += __builtin_popcountll(__builtin_amdgcn_ballot_w64(act[q]));
+    if ((threadIdx.x & (kWave - 1)) == 0) cnt[threadIdx.x / kWave] = jobs;
+    __syncthreads();
+    jobs = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / kWave; ++w) jobs += cnt[w];
+    if (jobs >= k) {  // else (fewer groups than k) every job is a candidate
+        bound_k = block_kth(mk, act, need, active, sh);
+        if (active > need) {
+            whole = false;
+            uint32_t w[PER];
+            uint32_t word[2];
+#pragma unroll
+            for (int part = 0; part < 2; ++part) {
+#pragma unroll
+                for (int q = 0; q < PER; ++q)
+                    w[q] = act[q] ? static_cast<uint32_t>(arrival_key(arrival[mi[q]]) >> (part ? 0 : 32)) : 0u;
+                word[part] = block_kth(w, act, need, active, sh);
             }
-            sk[r] = order_key(pred[j]);
-            sa[r] = arrival[j];
-            si[r] = j;
-        } else {
-            sk[r] = 0xffffffffu;
-            sa[r] = LLONG_MAX;
-            si[r] = INT_MAX;
+            bound_a = (static_cast<uint64_t>(word[0]) << 32) | word[1];
+#pragma unroll
+            for (int q = 0; q < PER; ++q) w[q] = static_cast<uint32_t>(mi[q]);
+            bound_i = static_cast<int>(block_kth(w, act, need, active, sh));
+        }
+    }
+    uint32_t* ck = ws.ckey + static_cast<size_t>(blockIdx.x) * ws.cap;
+    int32_t* ci = ws.cidx + static_cast<size_t>(blockIdx.x) * ws.cap;
+#pragma unroll
+    for (int s = 0; s < kSweeps; ++s) {
+        const int i0 = quad_first(blockIdx.x, s * kThreads + threadIdx.x);
+        if (s >= ws.sweeps || i0 >= n) continue;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int i = i0 + c;
+            const uint32_t key = order_key(v[s][c]);
+            bool in = i < n && (key < bound_k || (key == bound_k && whole));
+            if (i < n && key == bound_k && !whole) {
+                const uint64_t a = arrival_key(arrival[i]);
+                in = a < bound_a || (a == bound_a && i <= bound_i);
+            }
+            if (in) {
+                const int at = atomicAdd(&listed, 1);
+                ck[at] = key;
+                ci[at] = i;
+            }
         }
     }
     __syncthreads();
-    block_bitonic(sk, sa, si, P);
-    for (int r = threadIdx.x; r < k; r += kThreads) out_idx[r] = si[r];
+    if (threadIdx.x == 0) ws.count[blockIdx.x] = listed;
+}
+
+__global__ __launch_bounds__(kThreads) void select_rank_list_kernel(const int64_t* __restrict__ arrival, int k,
+                                                                    MinimaWs ws, int32_t* __restrict__ out_idx,
+                                                                    int32_t* __restrict__ out_count,
+                                                                    uint32_t* __restrict__ status) {
+    constexpr int J = 16;
+    __shared__ __attribute__((aligned(16))) uint32_t sk[kCandidates];
+    __shared__ uint32_t off[kMinWgs];
+    __shared__ uint32_t scan[kThreads];
+    __shared__ int part[kThreads / kWave][J];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    if (blockIdx.x == 0 && tid == 0) {
+        *out_count = k;
+        *status = 0u;
+    }
+    const int mine = tid < kMinWgs ? ws.count[tid] : 0;
+    int incl = mine;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int v = __shfl_up(incl, o, kWave);
+        if (lane >= o) incl += v;
+    }
+    if (lane == kWave - 1) scan[wid] = static_cast<uint32_t>(incl);
+    __syncthreads();
+    int total = 0;
+    for (int w = 0; w < kMinWgs / kWave; ++w) {
+        if (w < wid) incl += static_cast<int>(scan[w]);
+        total += static_cast<int>(scan[w]);
+    }
+    if (tid < kMinWgs) off[tid] = static_cast<uint32_t>(incl - mine);
+    __syncthreads();
+    if (static_cast<int>(blockIdx.x) * J >= total) return;  // uniform
+    const int n4 = (total + 3) / 4;
+    auto place = [&](int r) {
+        const int g = find_group(off, kMinWgs, static_cast<uint32_t>(r));
+        return static_cast<size_t>(g) * ws.cap + (r - static_cast<int>(off[g]));
+    };
+    for (int r = tid; r < 4 * n4; r += kThreads) sk[r] = r < total ? ws.ckey[place(r)] : 0xffffffffu;
+    __syncthreads();
+    const uint4* s4 = reinterpret_cast<const uint4*>(sk);
+    for (int i0 = blockIdx.x * J; i0 < total; i0 += gridDim.x * J) {
+        const int i = i0 + (tid & (J - 1));
+        const uint32_t ki = sk[i < total ? i : 0];
+        int below = 0;
+#pragma unroll 4
+        for (int q = tid / J; q < n4; q += kThreads / J) {
+            const uint4 v = s4[q];
+            below += static_cast<int>(v.x < ki) + static_cast<int>(v.y < ki) + static_cast<int>(v.z < ki) +
+                     static_cast<int>(v.w < ki);
+        }
+#pragma unroll
+        for (int o = J; o < kWave; o <<= 1) below += __shfl_xor(below, o, kWave);
+        if (lane < J) part[wid][lane] = below;
+        __syncthreads();
+        const int r = i0 + wid;  // one wave per job
+        int rank = k;
+        if (r < total) {
+            rank = 0;
+#pragma unroll
+            for (int w = 0; w < kThreads / kWave; ++w) rank += part[w][wid];
+        }
+        if (rank < k) {  // uniform over the wave
+            const uint32_t kr = sk[r];
+            const int32_t ir = ws.cidx[place(r)];
+            int ties = 0;
+#pragma unroll 4
+            for (int q = lane; q < n4; q += kWave) {
+                const uint4 v = s4[q];
+                const uint32_t e[4] = {v.x, v.y, v.z, v.w};
+                if ((v.x == kr) | (v.y == kr) | (v.z == kr) | (v.w == kr)) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const int j = 4 * q + c;
+                        if (e[c] == kr && j != r && j < total) {
+                            const int32_t ij = ws.cidx[place(j)];
+                            const int64_t ar = arrival[ir], aj = arrival[ij];
+                            ties += static_cast<int>((aj < ar) | ((aj == ar) & (ij < ir)));
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) ties += __shfl_xor(ties, o, kWave);
+            rank += ties;
+            if (lane == 0 && rank < k) out_idx[rank] = ir;
+        }
+        __syncthreads();  // part is written again
+    }
 }
 
 }  // namespace
@@ -637,6 +974,29 @@ size_t large_layout(int n, LargeWs* ws, char* base) {
     return o;
 }
 
+// Group-minima layout for n jobs, in the workspace of the radix path; returns its bytes.
+size_t minima_layout(int n, MinimaWs* ws, char* base) {
+    const int segments = (n + 15) / 16, per_wg = (segments + kMinWgs - 1) / kMinWgs, quads = 4 * per_wg;
+    MinimaWs w{};
+    w.cap = 16 * per_wg;
+    w.sweeps = (quads + kThreads - 1) / kThreads;
+    w.lanes = 1;
+    while (w.lanes * kMinGroups < (quads < kThreads ? quads : kThreads)) w.lanes <<= 1;
+    size_t o = align_up(sizeof(uint32_t));  // the status word
+    auto take = [&](size_t bytes) {
+        const size_t at = o;
+        o += align_up(bytes);
+        return base ? base + at : nullptr;
+    };
+    w.key = reinterpret_cast<uint32_t*>(take(4 * kMinWgs * kMinGroups));
+    w.idx = reinterpret_cast<int32_t*>(take(4 * kMinWgs * kMinGroups));
+    w.count = reinterpret_cast<int32_t*>(take(4 * kMinWgs));
+    w.ckey = reinterpret_cast<uint32_t*>(take(4 * static_cast<size_t>(kMinWgs) * w.cap));
+    w.cidx = reinterpret_cast<int32_t*>(take(4 * static_cast<size_t>(kMinWgs) * w.cap));
+    if (ws) *ws = w;
+    return o;
+}
+
 }  // namespace
 
 size_t select_workspace_bytes(int n) {
@@ -649,19 +1009,23 @@ hipError_t launch_select(const float* pred, const int64_t* arrival, int n, int k
                          int32_t* out_count, void* workspace, hipStream_t st) {
     if (n < 1 || n > kLargeMaxN || k < 0) return hipErrorInvalidValue;
     uint32_t* status = static_cast<uint32_t*>(workspace);
-    if (n <= kRankMaxN) {
-        const int threads = (n + kWave - 1) / kWave * kWave;  // one thread per job, whole waves
-        ELIS_TRY(launch_kernel(select_rank_kernel, dim3(1), dim3(threads), 0, st, pred, arrival, n, k, out_idx, out_count,
+    if (n <= kRankMaxN) return launch_rank(PlainJobs{pred, arrival, nullptr}, n, k, out_idx, out_count, status, st);
+    const int kk = k < n ? k : n;
+    if (kk > kSortMaxN) return hipErrorInvalidValue;
+    // Group minima while the candidates (k groups of at most lanes * 4 * sweeps jobs) fit the ranking kernel's LDS
+    // and at most half of the groups hold any (beyond, nearly every job becomes one), or where all jobs are few.
+    // This path against the radix path in us: 8,193 jobs 18 / 40 (k = 64) and 32 / 48 (k = 4,096); 20,000 jobs
+    // 18 / 40 (k = 64), 89 / 46 (k = 4,096, all of them candidates); 2^20 jobs 20 / 45 (k = 64).
+    MinimaWs mw;
+    const bool fits = minima_layout(n, &mw, static_cast<char*>(workspace)) <= large_layout(n, nullptr, nullptr);
+    const int most = kk * (mw.lanes * 4 * mw.sweeps);
+    if (kk > 0 && n <= kMinMaxN && fits && (n <= kMinAllN || (most <= kCandidates && 2 * most <= n))) {
+        ELIS_TRY(launch_kernel(select_minima_kernel, dim3(kMinWgs), dim3(kThreads), 0, st, pred, arrival, n, mw));
+        ELIS_TRY(launch_kernel(select_filter_kernel, dim3(kMinWgs), dim3(kThreads), 0, st, pred, arrival, n, kk, mw));
+        ELIS_TRY(launch_kernel(select_rank_list_kernel, dim3(kMinWgs), dim3(kThreads), 0, st, arrival, kk, mw, out_idx, out_count,
                                status));
         return hipSuccess;
     }
-    if (n <= kSortMaxN) {
-        ELIS_TRY(launch_kernel(select_sort_kernel, dim3(1), dim3(kThreads), 0, st, pred, arrival, n, k, out_idx, out_count,
-                           status));
-        return hipSuccess;
-    }
-    const int kk = k < n ? k : n;
-    if (kk > kSortMaxN) return hipErrorInvalidValue;
     LargeWs ws;
     large_layout(n, &ws, static_cast<char*>(workspace));
     ELIS_TRY(launch_kernel(select_init_kernel, dim3(1), dim3(256), 0, st, ws, kk, out_count));
@@ -674,8 +1038,28 @@ hipError_t launch_select(const float* pred, const int64_t* arrival, int n, int k
     ELIS_TRY(launch_kernel((select_count_kernel<0, 10>), grid, dim3(kBlock), 0, st, pred, n, ws));
     ELIS_TRY(launch_kernel((select_reduce_kernel<10>), red, dim3(1024), 0, st, ws));
     ELIS_TRY(launch_kernel(select_scatter_kernel, grid, dim3(kBlock), 0, st, pred, n, ws));
-    ELIS_TRY(launch_kernel(select_final_kernel, dim3(1), dim3(kThreads), 0, st, pred, arrival, kk, ws, out_idx));
-    return hipSuccess;
+    ELIS_TRY(launch_kernel(select_ties_kernel, dim3(1), dim3(kThreads), 0, st, arrival, ws));
+    return launch_rank(ListedJobs{pred, arrival, ws.picked}, kk, kk, out_idx, out_count, nullptr, st);
+}
+
+hipError_t launch_jobs_select(JobTable t, const int32_t* slots, const float* wait, float aging, int a, int k,
+                              int32_t* out_slots, int32_t* out_count, void* workspace, hipStream_t st) {
+    // Up to 1,024 candidates (one per thread) the ranking kernel gathers them itself: one launch instead of the
+    // gather, the select and the map back to slots.
+    if (a <= kThreads) return launch_rank(TableJobs{t, slots, wait, aging}, a, k, out_slots, out_count, nullptr, st);
+    const size_t n = static_cast<size_t>(a);
+    char* p = static_cast<char*>(workspace);
+    float* pred = reinterpret_cast<float*>(p);
+    int64_t* arr = reinterpret_cast<int64_t*>(p + align_up(4 * n));
+    int32_t* idx = reinterpret_cast<int32_t*>(p + align_up(4 * n) + align_up(8 * n));
+    void* sel_ws = p + align_up(4 * n) + align_up(8 * n) + align_up(4 * n);
+    // Bad slots are flagged in the table's status word: the select clears its own.
+    ELIS_TRY(launch_jobs_gather(t, slots, wait, aging, a, pred, arr, st));
+    if (a <= kRankMaxN)
+        return launch_rank(PlainJobs{pred, arr, slots}, a, k, out_slots, out_count, static_cast<uint32_t*>(sel_ws), st);
+    ELIS_TRY(launch_select(pred, arr, a, k, idx, out_count, sel_ws, st));
+    const int kk = k < a ? k : a;
+    return kk > 0 ? launch_jobs_map(slots, idx, out_count, kk, out_slots, st) : hipSuccess;
 }
 
 // ---------------------------------------------------------------------------------------------

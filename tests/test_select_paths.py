@@ -1,0 +1,69 @@
+"""Selection where its launch paths meet and where their bounds are reached, against the sort-based oracle.
+
+Up to 8,192 jobs are ranked directly; above, the candidates come from group minima while at most
+32,768 of them are possible (and at most half of the groups hold any), else from the radix selection. The data are the ones that these bounds depend on:
+in order, in reverse, all smallest jobs in few groups (every 4,096th job: the worst case), few
+distinct keys, one key (so that arrival and index decide), and NaN of both signs with infinities.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2505_09142_amd import _elis as E
+from tests.gpu_util import dev, note, ok, stream, workspace
+
+pytestmark = pytest.mark.gpu
+
+
+def data(kind, n, rng):
+    arr = rng.permutation(n).astype(np.int64)
+    if kind == "ascending":
+        return np.sort(rng.standard_normal(n).astype(np.float32)), arr
+    if kind == "descending":
+        return np.sort(rng.standard_normal(n).astype(np.float32))[::-1].copy(), arr
+    if kind == "clustered":  # the small keys in the jobs of few groups
+        p = rng.random(n).astype(np.float32) + 1.0
+        p[(np.arange(n) >> 4) % 256 == 3] -= 2.0
+        return p, arr
+    if kind == "few":
+        return rng.integers(0, 3, size=n).astype(np.float32), arr
+    if kind == "one":
+        return np.full(n, -3.5, np.float32), rng.integers(-n, n, size=n).astype(np.int64) << 33
+    bits = np.array([0x7FC00000, 0xFFC00001, 0x7F800000, 0xFF800000, 0x80000000, 0x00000000, 0x7F7FFFFF], np.uint32)
+    return rng.choice(bits, size=n).view(np.float32), arr
+
+
+def order(pred, arr):
+    u = pred.view(np.uint32).copy()
+    u[u == 0x80000000] = 0
+    key = np.where(u & 0x80000000, ~u, u | 0x80000000).astype(np.uint32)
+    key[np.isnan(pred)] = 0xFFFFFFFF
+    return np.lexsort((np.arange(len(pred)), arr, key))
+
+
+@pytest.mark.parametrize("kind", ["ascending", "descending", "clustered", "few", "one", "special"])
+@pytest.mark.parametrize("n,ks", [(15, (0, 1, 15)), (1025, (1, 1025)), (4096, (64, 4096)), (4097, (64, 5000)), (8192, (63, 8192)),
+                                  (8193, (1, 8192)), (12288, (64, 8192)), (12289, (8192,)), (24576, (8192,)), (32768, (1, 2048, 2049)), (32769, (64, 1024, 1025)),
+                                  (262145, (64, 256, 257, 512)), ((1 << 20) - 3, (64, 128, 129)), ((1 << 20) + 5, (64, 65)), (1 << 21, (1, 32, 64, 65)), ((1 << 21) + 1, (64,))])
+def test_select_at_the_edges(n, ks, kind):
+    rng = np.random.default_rng(n + len(kind))
+    pred, arr = data(kind, n, rng)
+    want = order(pred, arr)
+    base = dev(np.concatenate([np.zeros(1, np.float32), pred]))
+    buf, ws, wsb = workspace(E.elis_select_workspace_bytes(n))
+    d_arr = dev(arr)
+    for shift in (0, 1):  # the keys 16-byte aligned, and off by four bytes
+        d_pred = dev(pred) if shift == 0 else base[1:]
+        for k in ks:
+            note(f"select n={n} kind={kind} k={k} shift={shift}")
+            idx = torch.full((max(1, k) + 8,), -1, dtype=torch.int32, device="cuda")
+            cnt = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+            ok(E.elis_isrtf_select(d_pred.data_ptr(), d_arr.data_ptr(), n, k, idx.data_ptr(), cnt.data_ptr(), ws,
+                                   E.elis_select_workspace_bytes(n), stream()), "select")
+            torch.cuda.synchronize()
+            m = min(k, n)
+            assert int(cnt.item()) == m
+            got = idx.cpu().numpy()
+            assert np.array_equal(got[:m], want[:m]) and np.all(got[m:] == -1)
+    st, bits = E.elis_read_status(ws, stream())
+    assert st == E.ELIS_OK and bits == 0
