@@ -318,7 +318,9 @@ int elis_linear(const uint16_t *x, const uint16_t *w, const float *bias, const f
  * the three rest fields are 0). The plan comes from a launch-time model of the
  * tile configurations and the device's compute-unit count; every plan gives
  * bit-identical results (except that the 128 x 64 tile, used only when n is
- * an odd multiple of 64, accumulates with 16 x 16 x 32 blocks). Errors: as
+ * an odd multiple of 64, accumulates with 16 x 16 x 32 blocks). Few rows (at
+ * most 512 tiles of 32 x 32) run in one launch of such tiles instead where the
+ * model prices it below the plan, with the same bits. Errors: as
  * elis_linear (ELIS_EINVAL, ELIS_EUNSUPPORTED), and ELIS_EINVAL on a null out.
  */
 int elis_linear_plan(int32_t m, int32_t n, int32_t k, int32_t epilogue, int32_t *out);

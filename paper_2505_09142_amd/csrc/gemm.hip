@@ -6,8 +6,9 @@
 // either an fp32 matrix or a LayerNorm output rebuilt from its pre-norm rows and
 // row statistics (Residual in kernels.h).
 //
-// Three kernels; launch_gemm plans each product (plan_gemm: one launch, or a
-// launch of large tiles over whole rounds plus one of small tiles over the remaining rows):
+// Four kernels; launch_gemm plans each product (plan_gemm: one launch, or a
+// launch of large tiles over whole rounds plus one of small tiles over the remaining rows;
+// gemm_few_rows: 32 x 32 tiles instead):
 //   gemm_kernel        register-staged k-slabs, 16 x 16 x 32 MFMA blocks; for N that
 //                      is an odd multiple of 64;
 //   gemm_sched_kernel  k-slabs go HBM -> LDS with global_load_lds_dwordx4 (no register
@@ -17,7 +18,8 @@
 //                      epilogue staged through LDS for full-line stores; tiles of
 //                      128 x 128, 64 x 128 and 64 x 64;
 //   gemm_persist_kernel  256 x 256 tiles, one persistent work-group per CU whose two wave
-//                      groups alternate between reading fragments and multiplying.
+//                      groups alternate between reading fragments and multiplying;
+//   gemm_wave_kernel     32 x 32 tiles, one wave each, for products of few rows.
 //
 // LDS layout. A k-slab row of 64 bf16 is eight 16-byte chunks; the chunk index
 // is XOR-swizzled with the row so the rows one MFMA operand read touches fall on
@@ -822,6 +824,140 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #endif
 }
 
+// ---------------------------------------------------------------------------------------------
+// 32 x 32 tiles, one wave per work-group: products of few rows, where a wider tile would leave most
+// CUs without one. The wave keeps seven 64-deep k-slabs (8 KB each) in flight into a ring of eight in
+// LDS; nobody else reads them, so there is no barrier. Fragments of the next slab are read while the
+// current one is multiplied, and the residual, bias and LayerNorm columns are requested up front.
+// Bound by the CU's load path (8 KB per slab at about 37 bytes a cycle, 0.105 us; it takes 0.125):
+// the 64 x 64 tile moves 16 KB per slab on a quarter of the CUs. That tile (four-stage, 0.22 us per
+// slab) took 13.1 us at 193 x 768 x 3,072, this one 8.9; 64 rows 13.0 -> 8.7, 512 rows 13.7 -> 9.7;
+// 193 x 768 x 768 5.4 -> 4.3. Past 512 tiles (two per CU) the wider tiles win: 193 x 3,072 x 768, 672
+// tiles, 5.5 against 7.8.
+template <int EPI>
+__global__ __launch_bounds__(64) void gemm_wave_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
+                                                       const float* __restrict__ bias, Residual res,
+                                                       void* __restrict__ out, int M, int N, int K) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass has no buffer-resource type
+    constexpr int RING = 8, SLAB = 64 * kBK;
+    constexpr bool F32OUT = kF32Out<EPI>;
+    __shared__ __attribute__((aligned(1024))) uint16_t smem[RING * SLAB];
+    const int tiles_m = (M + 31) / 32, t = xcd_remap(blockIdx.x, tiles_m * (N / 32));
+    const int m0 = (t % tiles_m) * 32, n0 = (t / tiles_m) * 32;  // an XCD's work-groups share few weight rows
+    const int lane = threadIdx.x, rl = lane & 31, kg = lane >> 5;
+    const int rows = M - m0 < 32 ? M - m0 : 32, KT = K / kBK;
+
+    const int m = m0 + (rl < rows ? rl : rows - 1);  // rows past the end compute on the last row, stored nowhere
+    f32x4 bv[4], hv[4], gv[4], cv[4];
+    float2 sv;
+    // Buffer loads, which the compiler leaves ahead of the slabs' loads instead of moving them to their use.
+    auto early = [&](const float* p, size_t base, uint32_t off) {
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p) + base, 0, 0xffffffffu, 0x00020000);
+        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off * 4u, 0, 0));
+    };
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t n = 8 * q + 4 * kg;
+        bv[q] = early(bias, n0, n);
+        if constexpr (F32OUT) hv[q] = early(res.x, static_cast<size_t>(m0) * N + n0, (m - m0) * N + n);
+        if constexpr (kResLn<EPI>) {
+            gv[q] = early(res.g, n0, n);
+            cv[q] = early(res.b, n0, n);
+        }
+    }
+    if constexpr (kResLn<EPI>) {
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(res.stats) + m0, 0, rows * 8, 0x00020000);
+        sv = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, (m - m0) * 8, 0, 0));
+    }
+
+    uint32_t oa[4], ob[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = i * 8 + (lane >> 3), c = ((lane & 7) ^ swz(r)) * 8;
+        oa[i] = static_cast<uint32_t>(((r < rows ? r : rows - 1) * K + c) * 2);
+        ob[i] = static_cast<uint32_t>((r * K + c) * 2);
+    }
+    // Past the last slab the resource is empty (no memory access), so that every step runs the same code.
+    auto load = [&](int kt) {
+        const bool more = kt < KT;
+        const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint16_t*>(A) + static_cast<size_t>(m0) * K, 0, more ? rows * K * 2 : 0, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint16_t*>(B) + static_cast<size_t>(n0) * K, 0, more ? 32 * K * 2 : 0, 0x00020000);
+        const int at = more ? kt * kBK * 2 : 0;
+        uint16_t* d = smem + (kt % RING) * SLAB;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t*)(d + i * 8 * kBK), 16, oa[i], at, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void_t*)(d + (4 + i) * 8 * kBK), 16, ob[i], at, 0, 0);
+    };
+    int lo[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) lo[ks] = rl * kBK + (((ks * 2 + kg) ^ swz(rl)) * 8);
+    bf16x8 fa[2][4], fb[2][4];
+    auto read = [&](int buf, int kt) {
+        const uint16_t* p = smem + (kt % RING) * SLAB;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            fa[buf][ks] = *reinterpret_cast<const bf16x8*>(p + lo[ks]);
+            fb[buf][ks] = *reinterpret_cast<const bf16x8*>(p + 32 * kBK + lo[ks]);
+        }
+    };
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+    for (int p = 0; p < RING - 1; ++p) load(p);
+    wait_vmcnt<(RING - 2) * 8>();
+    read(0, 0);
+    // Slab kt: request slab kt + 7 (into the slot of slab kt - 1, whose fragments have been multiplied),
+    // wait for slab kt + 1 and read its fragments, multiply.
+    auto step = [&](int buf, int kt) {
+        load(kt + RING - 1);
+        wait_vmcnt<(RING - 2) * 8>();
+        read(buf ^ 1, kt + 1);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) acc = Mfma<32>::run(fb[buf][ks], fa[buf][ks], acc);
+    };
+    int kt = 0;
+    for (; kt + 1 < KT; kt += 2) {
+        step(0, kt);
+        step(1, kt + 1);
+    }
+    if (kt < KT) step(0, kt);
+    wait_vmcnt<0>();  // the empty loads write LDS: none may outlive the work-group
+
+    if (rl >= rows) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const size_t o = static_cast<size_t>(m) * N + n0 + 8 * q + 4 * kg;
+        f32x4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = acc[4 * q + r];
+        v += bv[q];
+        if constexpr (F32OUT) {
+            f32x4 h = hv[q];
+            if constexpr (kResLn<EPI>) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) h[c] = fmaf((h[c] - sv.x) * sv.y, gv[q][c], cv[q][c]);
+            }
+            *reinterpret_cast<f32x4*>(static_cast<float*>(out) + o) = v + h;
+        } else {
+            if constexpr (EPI == ELIS_EPI_BIAS_GELU_BF16) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = gelu_erf(v[c]);
+            }
+            u32x2 pk;
+            pk[0] = pack_bf16x2(v[0], v[1]);
+            pk[1] = pack_bf16x2(v[2], v[3]);
+            *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(out) + o) = pk;
+        }
+    }
+#endif
+}
+
 hipError_t launch_persist(const uint16_t* x, const uint16_t* w, const float* bias, Residual res, int m, int n, int k,
                            int epi, void* out, hipStream_t st, int group_m) {
     const int tiles = ((m + 255) / 256) * (n / 256), cus = device_cus();
@@ -833,6 +969,20 @@ hipError_t launch_persist(const uint16_t* x, const uint16_t* w, const float* bia
         case ELIS_EPI_BIAS_RES_F32: return go(gemm_persist_kernel<ELIS_EPI_BIAS_RES_F32>);
         case kEpiResLn: return go(gemm_persist_kernel<kEpiResLn>);
         case kEpiResLnFfn2: return go(gemm_persist_kernel<kEpiResLnFfn2>);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_wave(const uint16_t* x, const uint16_t* w, const float* bias, Residual res, int m, int n, int k,
+                       int epi, void* out, hipStream_t st) {
+    const dim3 grid(((m + 31) / 32) * (n / 32)), block(kWave);
+    auto go = [&](auto kernel) { return launch_kernel(kernel, grid, block, 0, st, x, w, bias, res, out, m, n, k); };
+    switch (epi) {
+        case ELIS_EPI_BIAS_BF16: return go(gemm_wave_kernel<ELIS_EPI_BIAS_BF16>);
+        case ELIS_EPI_BIAS_GELU_BF16: return go(gemm_wave_kernel<ELIS_EPI_BIAS_GELU_BF16>);
+        case ELIS_EPI_BIAS_RES_F32: return go(gemm_wave_kernel<ELIS_EPI_BIAS_RES_F32>);
+        case kEpiResLn: return go(gemm_wave_kernel<kEpiResLn>);
+        case kEpiResLnFfn2: return go(gemm_wave_kernel<kEpiResLnFfn2>);
         default: return hipErrorInvalidValue;
     }
 }
@@ -965,7 +1115,15 @@ constexpr TileModel kTileModels[] = {
     {36, 64, 64, 2, 4, {0.218f, 0.237f, 0.377f, 0.380f},
      {{2.83f, 2.93f, 3.18f, 1.29f}, {3.29f, 3.07f, 3.61f, 1.50f}, {3.35f, 3.86f, 4.78f, 2.16f}}},
 };
+// The one-wave 32 x 32 tile, up to one round and never beside another launch (beta unused).
+constexpr TileModel kWaveModel = {0, 32, 32, 2, 1, {0.125f, 0.126f, 0.176f, 0.f},
+                                  {{2.62f, 2.83f, 2.66f, 0.f}, {2.88f, 3.09f, 2.94f, 0.f}, {2.68f, 2.82f, 3.04f, 0.f}}};
 constexpr float kSecondLaunchUs = 1.0f;  // dispatch cost of the remainder launch
+
+int epilogue_kind(int epi) {
+    if (epi == ELIS_EPI_BIAS_RES_F32 || kResLnCode(epi)) return 2;
+    return epi == ELIS_EPI_BIAS_GELU_BF16 ? 1 : 0;
+}
 
 double model_us(const TileModel& t, int kind, long long m, int n, int k, long long cus) {
     if (m <= 0) return 0.0;
@@ -992,10 +1150,10 @@ double model_us(const TileModel& t, int kind, long long m, int n, int k, long lo
 // as two rounds of the 128 x 128 pairs, but a round that is only partly filled costs nearly a
 // full one, so the rows past the last full round of large tiles go to a configuration whose
 // tiles are small enough to finish them in one short round.
-GemmPlan plan_gemm(int m, int n, int k, int epi) {
-    const bool f32out = epi == ELIS_EPI_BIAS_RES_F32 || kResLnCode(epi);
+GemmPlan plan_gemm(int m, int n, int k, int epi, double* us) {
+    if (us) *us = 0.0;
     if (n % 128 != 0) return {1, m, 0};
-    const int kind = f32out ? 2 : (epi == ELIS_EPI_BIAS_GELU_BF16 ? 1 : 0);
+    const int kind = epilogue_kind(epi);
     const long long cus = device_cus();
     GemmPlan best{21, m, 0};
     double best_us = -1.0;
@@ -1021,7 +1179,16 @@ GemmPlan plan_gemm(int m, int n, int k, int epi) {
             }
         }
     }
+    if (us) *us = best_us;
     return best;
+}
+
+// Whether the product runs in 32 x 32 tiles: where those fill at most one round (512 tiles) and the model prices
+// them below the plan. That is up to about 540 rows at n = 768 or 1,024, 200 at n = 2,304 and 150 at n = 3,072
+// or 4,096.
+bool gemm_few_rows(int m, int n, int k, int epi, double plan_us) {
+    if (n % 128 != 0 || k > (1 << 21) || n > (1 << 20)) return false;  // 32-bit offsets inside a tile's operands
+    return model_us(kWaveModel, epilogue_kind(epi), m, n, k, device_cus()) < plan_us;
 }
 
 hipError_t launch_gemm_plan(const GemmPlan& p, const uint16_t* x, const uint16_t* w, const float* bias,
@@ -1045,7 +1212,10 @@ hipError_t launch_gemm_plan(const GemmPlan& p, const uint16_t* x, const uint16_t
 hipError_t launch_gemm(const uint16_t* x, const uint16_t* w, const float* bias, Residual res, int m, int n,
                        int k, int epi, void* out, hipStream_t st) {
     if (m < 1 || n % 64 != 0 || k % kBK != 0 || n < 64 || k < kBK) return hipErrorInvalidValue;
-    return launch_gemm_plan(plan_gemm(m, n, k, epi), x, w, bias, res, m, n, k, epi, out, st);
+    double us = 0.0;
+    const GemmPlan p = plan_gemm(m, n, k, epi, &us);
+    if (gemm_few_rows(m, n, k, epi, us)) return launch_wave(x, w, bias, res, m, n, k, epi, out, st);
+    return launch_gemm_plan(p, x, w, bias, res, m, n, k, epi, out, st);
 }
 
 }  // namespace elis

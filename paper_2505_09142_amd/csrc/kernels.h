@@ -53,12 +53,13 @@ constexpr int kEpiResLnFfn2 = 5;
 hipError_t launch_gemm(const uint16_t* x, const uint16_t* w, const float* bias, Residual res, int m, int n,
                        int k, int epi, void* out, hipStream_t st);
 
-// Launch plan of one product (gemm.hip): rows [0, m1) with configuration `main`, then, when
+// Tile plan of one product (gemm.hip; launch_gemm may run few rows in 32 x 32 tiles instead): rows [0, m1) with configuration `main`, then, when
 // m1 < M, rows [m1, M) with configuration `rest`.
 struct GemmPlan {
     int main, m1, rest;
 };
-GemmPlan plan_gemm(int m, int n, int k, int epi);
+// us: the model's time for it (0 where it prices none), or null.
+GemmPlan plan_gemm(int m, int n, int k, int epi, double* us = nullptr);
 hipError_t launch_gemm_plan(const GemmPlan& p, const uint16_t* x, const uint16_t* w, const float* bias,
                             Residual res, int m, int n, int k, int epi, void* out, hipStream_t st);
 // Tile of a configuration (zeros if unknown) and the configuration of a tile (-1 if none).
