@@ -340,14 +340,18 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4
         bf16x8 pf[2][2];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            float mx = fmaxf(fmaxf(sc[0][j][0], sc[0][j][1]), fmaxf(sc[0][j][2], sc[0][j][3]));
-#pragma unroll
-            for (int tt = 1; tt < 4; ++tt)
-                mx = fmaxf(mx, fmaxf(fmaxf(sc[tt][j][0], sc[tt][j][1]), fmaxf(sc[tt][j][2], sc[tt][j][3])));
-            mx = quad_max(mx);
+            // Maximum of the lane's 16 scores, three values an instruction. Whether any query of the block
+            // grew needs no exchange between the four lanes of a query: that follows only if one did.
+            auto at = [&](int e) { return sc[e >> 2][j][e & 3]; };
+            float ma = fmaxf(fmaxf(at(0), at(1)), at(2)), mb = fmaxf(fmaxf(at(7), at(8)), at(9));
+            ma = fmaxf(fmaxf(ma, at(3)), at(4));
+            mb = fmaxf(fmaxf(mb, at(10)), at(11));
+            ma = fmaxf(fmaxf(ma, at(5)), at(6));
+            mb = fmaxf(fmaxf(mb, at(12)), at(13));
+            const float mx = fmaxf(fmaxf(fmaxf(ma, mb), at(14)), at(15));
             // m_run = -inf on the first tile: every query grows (each tile holds a valid key).
             if (__builtin_amdgcn_ballot_w64(mx > m_run[j] + lag) != 0) {
-                const float m_new = fmaxf(m_run[j], mx);
+                const float m_new = fmaxf(m_run[j], quad_max(mx));
                 const float alpha = __builtin_amdgcn_exp2f((m_run[j] - m_new) * scale_log2);
                 m_run[j] = m_new;
 #pragma unroll

@@ -18,6 +18,7 @@ namespace elis {
 namespace {
 
 constexpr int kThreads = 1024;
+constexpr int kDirect = 256;  // most sequences whose work list is counted directly
 constexpr int kBuckets = 64;  // sort key: 64-key tiles per sequence, capped
 static_assert(kBuckets == kWave, "one bucket per lane in the per-wave bucket totals");
 
@@ -33,6 +34,84 @@ __device__ __forceinline__ int wave_incl_scan(int v, int lane) {
         if (lane >= o) v += u;
     }
     return v;
+}
+
+// Up to kDirect sequences: every sequence counts the tiles listed before its own (and before it in the
+// batch), 1,024 / p2 threads sharing the count (p2 = n rounded up to a power of two): two barriers and one round
+// of loads, where the chunked kernel below scans, then walks a wave's 64 sequences one by one.
+// Bound by launch and load latency: 64 sequences 8.0 -> 5.3 us.
+__global__ __launch_bounds__(kThreads) void seqmap_direct_kernel(const int32_t* __restrict__ cu, int n, int total,
+                                                                 int max_seqlen, int32_t* __restrict__ start,
+                                                                 int32_t* __restrict__ len,
+                                                                 int32_t* __restrict__ tile_off,
+                                                                 int32_t* __restrict__ work, int work_cap,
+                                                                 uint32_t* __restrict__ status) {
+    __shared__ int4 item[kDirect];  // bucket, tiles, start, length
+    __shared__ int listed[kDirect], batch[kDirect];  // tiles before the sequence's, in the list and in the batch
+    __shared__ uint32_t bad[kDirect / kWave];
+    __shared__ int all_s;
+    const int tid = threadIdx.x;
+    if (tid == 0) all_s = 0;
+    if (tid < kDirect) {  // whole waves
+        uint32_t flags = 0;
+        if (tid < n) {
+            const int max_len = max_seqlen < total ? max_seqlen : total;
+            int a = cu[tid];
+            const int b = cu[tid + 1];
+            if (tid == 0 && a != 0) flags |= ELIS_DEV_BAD_CU;
+            if (tid == n - 1 && b != total) flags |= ELIS_DEV_BAD_CU;
+            int L = b - a;
+            if (L < 1) flags |= ELIS_DEV_BAD_CU;
+            if (L > max_seqlen) flags |= ELIS_DEV_LONG_SEQ;
+            L = L < 1 ? 1 : (L > max_len ? max_len : L);
+            a = a < 0 ? 0 : (a > total - L ? total - L : a);
+            start[tid] = a;
+            len[tid] = L;
+            item[tid] = make_int4(len_bucket(L), (L + kAttnRowsPerBlock - 1) / kAttnRowsPerBlock, a, L);
+        }
+        listed[tid] = batch[tid] = 0;
+        const uint64_t cu_bad = __builtin_amdgcn_ballot_w64((flags & ELIS_DEV_BAD_CU) != 0);
+        const uint64_t len_bad = __builtin_amdgcn_ballot_w64((flags & ELIS_DEV_LONG_SEQ) != 0);
+        if ((tid & (kWave - 1)) == 0) bad[tid / kWave] = (cu_bad ? ELIS_DEV_BAD_CU : 0u) | (len_bad ? ELIS_DEV_LONG_SEQ : 0u);
+    }
+    __syncthreads();
+    int p2 = 1;
+    while (p2 < n) p2 <<= 1;
+    const int s = tid & (p2 - 1), first = tid / p2, step = kThreads / p2;
+    if (s < n) {
+        const int b = item[s].x;
+        int l = 0, q = 0, all = 0;
+        for (int j = first; j < n; j += step) {
+            const int ob = item[j].x, ot = item[j].y;
+            all += ot;
+            q += j < s ? ot : 0;
+            l += (ob > b) | ((ob == b) & (j < s)) ? ot : 0;
+        }
+        // Whole numbers: the same sums in any order.
+        atomicAdd(&listed[s], l);
+        atomicAdd(&batch[s], q);
+        if (s == 0) atomicAdd(&all_s, all);
+    }
+    __syncthreads();
+    const int all = all_s;
+    if (tid == 0) {
+        uint32_t flags = 0;
+        for (int w = 0; w < kDirect / kWave; ++w) flags |= bad[w];
+        *status = flags;
+        tile_off[n] = all;
+    }
+    if (tid < n) tile_off[tid] = batch[tid];
+    if (!work) return;  // uniform
+    for (int idx = all + tid; idx < work_cap; idx += kThreads)  // unused slots: length 0
+        *reinterpret_cast<int4*>(work + 4 * static_cast<size_t>(idx)) = make_int4(0, 0, 0, 0);
+    if (s < n) {  // the threads of a sequence write its tiles in turn
+        const int4 e = item[s];
+        for (int q = first; q < e.y; q += step) {
+            const int idx = listed[s] + q;
+            if (idx < work_cap)
+                *reinterpret_cast<int4*>(work + 4 * static_cast<size_t>(idx)) = make_int4(e.z, e.w, q * kAttnRowsPerBlock, s);
+        }
+    }
 }
 
 __global__ __launch_bounds__(kThreads) void seqmap_kernel(const int32_t* __restrict__ cu, int n, int total,
@@ -152,6 +231,9 @@ __global__ __launch_bounds__(kThreads) void seqmap_kernel(const int32_t* __restr
 
 hipError_t launch_seqmap(const int32_t* cu, int n, int total, int max_seqlen, SeqTable tab, uint32_t* status,
                          hipStream_t st) {
+    if (n <= kDirect)
+        return launch_kernel(seqmap_direct_kernel, dim3(1), dim3(kThreads), 0, st, cu, n, total, max_seqlen, tab.start,
+                             tab.len, tab.tile_off, tab.work, attn_work_capacity(n, total), status);
     ELIS_TRY(launch_kernel(seqmap_kernel, dim3(1), dim3(kThreads), 0, st, cu, n, total, max_seqlen, tab.start,
                        tab.len, tab.tile_off, tab.work, attn_work_capacity(n, total), status));
     return hipSuccess;
