@@ -4,7 +4,7 @@
 //
 // Work decomposition. A work-group takes one (sequence, head, 128-query tile);
 // the tile table built by the seq-map kernel maps blockIdx.x to its sequence.
-// Each of the 4 waves owns 32 queries (two 16-query MFMA blocks) and streams
+// Each of the 4 waves owns 32 queries (two 16-query MFMA blocks; one block where the launch is small) and streams
 // the sequence's keys and values through LDS in 64-token tiles, keeping a
 // running maximum and running sum per query (online softmax), so the score
 // matrix never leaves registers.
@@ -41,10 +41,12 @@ namespace elis {
 namespace {
 
 constexpr int kWaves = 4;
-constexpr int kQPerWave = 32;
-constexpr int kBQ = kWaves * kQPerWave;  // == kAttnRowsPerBlock
+constexpr int kBQ = kWaves * 32;  // == kAttnRowsPerBlock: two 16-query blocks per wave
 constexpr int kBKV = 64;
 constexpr int kVtStride = kBKV + 8;
+// Work-groups of 128 queries, per two CUs, up to which each runs as two of 64: 528 of them (256 CUs) 17.6 us for the
+// wide and 14.9 for the narrow form, 684 19.0 / 18.5, 752 long ones 38.6 / 40.8, 2,000 97 / 111.
+constexpr int kNarrowMax = 5;
 static_assert(kBQ == kAttnRowsPerBlock, "tile table and kernel must agree");
 
 template <int DH>
@@ -82,15 +84,15 @@ __device__ __forceinline__ float quad_max(float v) {
     return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));  // {l & 31, l | 32}
 }
 
-// Four waves per SIMD (at most 128 VGPRs): with 32 KB of LDS per work-group, four work-groups
-// share a CU and cover one another's tile loads and barriers.
-template <int DH, bool CLS>
-__global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4))) void attention_kernel(
+// One work-group: QB 16-query blocks per wave, 64 QB queries of a (query tile, head).
+template <int DH, bool CLS, int QB>
+__device__ __forceinline__ void attention_block(
     const uint16_t* __restrict__ qkv, const int32_t* __restrict__ seq_start, const int32_t* __restrict__ seq_len,
     const int32_t* __restrict__ work, int H, uint16_t* __restrict__ out, float scale_log2, int total) {
 // The body is device code only: the host pass has no buffer-resource type, and a kernel whose
 // body it cannot form would lose its host-side launch stub.
 #if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int kQPerWave = 16 * QB;
     constexpr int CPR = DH / 8;   // 16-byte chunks per head row
     constexpr int KS = DH / 32;   // MFMA k-steps over d_head
     constexpr int DT = DH / 16;   // 16-wide d blocks of the output
@@ -105,11 +107,13 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4
 
     // Work-group w runs head w % H of work item w / H: the heads of one query tile are
     // adjacent, and the items come longest sequence first (the work list's order; slots
-    // past the list's end hold length 0). CLS: item s is sequence s, one work-group per
-    // (sequence, head) computing the first 32 queries (wave 0, exactly as in the full launch,
-    // so the CLS query sees the same arithmetic) and writing the CLS row alone, to row s of a
-    // one-row-per-sequence output.
-    const int item = blockIdx.x / H, h = blockIdx.x - item * H;
+    // past the list's end hold length 0). With QB 1 two work-groups share an item, 64 queries each.
+    // CLS: item s is sequence s, one work-group per (sequence, head) computing the first 16 queries
+    // (wave 0; a block's arithmetic depends on its own 16 queries only, so the CLS query sees the same
+    // as in the full launch) and writing the CLS row alone, to row s of a one-row-per-sequence output.
+    constexpr int PARTS = CLS || QB == 2 ? 1 : 2;
+    const int unit = blockIdx.x / PARTS;
+    const int item = unit / H, h = unit - item * H;
     int s, seq0, L, q0;
     if constexpr (CLS) {
         s = item;
@@ -120,9 +124,9 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4
         const int4 e = *reinterpret_cast<const int4*>(work + 4 * static_cast<size_t>(item));
         seq0 = e.x;
         L = e.y;
-        q0 = e.z;
+        q0 = e.z + (blockIdx.x - unit * PARTS) * (kWaves * kQPerWave);
         s = e.w;
-        if ((L <= 0) | (q0 < 0)) return;  // uniform; q0 >= 0 always, tested so the entry is loaded whole here
+        if ((L <= 0) | (e.z < 0) | (q0 >= L)) return;  // uniform; e.z >= 0 always, tested so the entry is loaded whole here
     }
     const int q_end = CLS ? (L < kQPerWave ? L : kQPerWave) : L;  // queries computed
 
@@ -137,9 +141,9 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4
     const float lag = 8.0f / scale_log2;  // raw-score lag of the lazy running maximum
 
     // Query fragments (B operand of S^T = K Q^T): lane holds Q[query][8 d's of its k-group].
-    bf16x8 qf[2][KS];
+    bf16x8 qf[QB][KS];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < QB; ++j) {
         int qi = qw + j * 16 + r16;
         qi = qi < L ? qi : L - 1;
         const uint16_t* row = Qg + static_cast<size_t>(seq0 + qi) * D3;
@@ -147,13 +151,15 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4
         for (int ks = 0; ks < KS; ++ks) qf[j][ks] = *reinterpret_cast<const bf16x8*>(row + ks * 32 + 8 * g);
     }
 
-    f32x4 o[DT][2];
+    f32x4 o[DT][QB], lsum[QB];  // lsum: row sums (every register)
+    float m_run[QB];
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+    for (int j = 0; j < QB; ++j) {
+        lsum[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        m_run[j] = -INFINITY;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) o[dt][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 lsum[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};  // row sums (every register)
-    float m_run[2] = {-INFINITY, -INFINITY};
+        for (int dt = 0; dt < DT; ++dt) o[dt][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     bf16x8 ones;
 #pragma unroll
     for (int e = 0; e < 8; ++e) ones[e] = static_cast<__bf16>(1.0f);
@@ -296,8 +302,8 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4
 
         if (qw >= q_end) return;  // this wave's queries are all past the end (uniform per wave)
 
-        // S^T = K Q^T: 4 key blocks x 2 query blocks (raw scores, unscaled).
-        f32x4 sc[4][2];
+        // S^T = K Q^T: 4 key blocks x QB query blocks (raw scores, unscaled).
+        f32x4 sc[4][QB];
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
             const int row = tt * 16 + r16;
@@ -308,7 +314,7 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4
                 kf[ks] = *reinterpret_cast<const bf16x8*>(&k_s[row * DH + ((ch ^ kswz<DH>(row)) * 8)]);
             }
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < QB; ++j) {
                 f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks)
@@ -323,8 +329,8 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     if (tt * 16 + 4 * g + r >= valid) {
-                        sc[tt][0][r] = -INFINITY;
-                        sc[tt][1][r] = -INFINITY;
+#pragma unroll
+                        for (int j = 0; j < QB; ++j) sc[tt][j][r] = -INFINITY;
                     }
         }
 
@@ -337,9 +343,9 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4
         // fp32 sums hold with the same relative precision, and nothing is rescaled: after the
         // first tile a block rarely rescales again (with an exact running maximum nearly every
         // tile raised some query's maximum).
-        bf16x8 pf[2][2];
+        bf16x8 pf[2][QB];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < QB; ++j) {
             // Maximum of the lane's 16 scores, three values an instruction. Whether any query of the block
             // grew needs no exchange between the four lanes of a query: that follows only if one did.
             auto at = [&](int e) { return sc[e >> 2][j][e & 3]; };
@@ -395,14 +401,14 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4
                     vf = *reinterpret_cast<const bf16x8*>(&v_s[d * kVtStride + kc * 32 + 8 * g]);
                 }
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < QB; ++j)
                     o[dt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[kc][j], o[dt][j], 0, 0, 0);
             }
         }
 #pragma unroll
         for (int kc = 0; kc < 2; ++kc)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) lsum[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[kc][j], lsum[j], 0, 0, 0);
+            for (int j = 0; j < QB; ++j) lsum[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[kc][j], lsum[j], 0, 0, 0);
     };
     for (int t = 0; t < ntiles; t += 2) {
         tile(t, sK0, sV0, sK1, sV1);
@@ -411,7 +417,7 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4
 
     // Normalise and store: lane holds O[query j*16 + r16][d = dt*16 + 4g .. +3].
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < QB; ++j) {
         const float inv = 1.0f / lsum[j][0];
         const int qi = qw + j * 16 + r16;
         if (CLS ? qi != 0 : qi >= L) continue;
@@ -427,6 +433,26 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4
 #endif
 }
 
+// Four waves per SIMD (at most 128 VGPRs): with 32 KB of LDS per work-group, four work-groups
+// share a CU and cover one another's tile loads and barriers. The CLS-only tail needs one block.
+template <int DH, bool CLS>
+__global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4))) void attention_kernel(
+    const uint16_t* __restrict__ qkv, const int32_t* __restrict__ seq_start, const int32_t* __restrict__ seq_len,
+    const int32_t* __restrict__ work, int H, uint16_t* __restrict__ out, float scale_log2, int total) {
+    attention_block<DH, CLS, CLS ? 1 : 2>(qkv, seq_start, seq_len, work, H, out, scale_log2, total);
+}
+
+// One 16-query block per wave, for launches that leave the CUs with few work-groups: a wave alone on its SIMD
+// takes as long per key tile as its own chain of products, maxima and exponentials, and half the
+// queries are half the chain: 192 work-groups of up to 8 key tiles 13.6 -> 11.7 us with the sequence map, 432 of
+// up to 32 tiles 36 -> 32. (Three tiles in flight instead of one changed nothing: the loads are covered.)
+template <int DH>
+__global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(4))) void attention_narrow_kernel(
+    const uint16_t* __restrict__ qkv, const int32_t* __restrict__ seq_start, const int32_t* __restrict__ seq_len,
+    const int32_t* __restrict__ work, int H, uint16_t* __restrict__ out, float scale_log2, int total) {
+    attention_block<DH, false, 1>(qkv, seq_start, seq_len, work, H, out, scale_log2, total);
+}
+
 }  // namespace
 
 hipError_t launch_attention(const uint16_t* qkv, SeqTable tab, int n, int total, int heads, int dh, uint16_t* out,
@@ -436,16 +462,17 @@ hipError_t launch_attention(const uint16_t* qkv, SeqTable tab, int n, int total,
     if (!cls_only && !tab.work) return hipErrorInvalidValue;
     const int items = cls_only ? n : attn_work_capacity(n, total);
     if (static_cast<long long>(items) * heads > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid(items * heads), block(kWaves * kWave);
+    const bool narrow = !cls_only && static_cast<long long>(items) * heads * 2 <= kNarrowMax * static_cast<long long>(device_cus());
+    const dim3 grid(items * heads * (narrow ? 2 : 1)), block(kWaves * kWave);
     const float scale_log2 = 1.4426950408889634f / sqrtf(static_cast<float>(dh));
     auto go = [&](auto kernel) {
         return launch_kernel(kernel, grid, block, 0, st, qkv, tab.start, tab.len, tab.work, heads, out, scale_log2,
                              total);
     };
     if (dh == 64)
-        ELIS_TRY(cls_only ? go(attention_kernel<64, true>) : go(attention_kernel<64, false>));
+        ELIS_TRY(cls_only ? go(attention_kernel<64, true>) : narrow ? go(attention_narrow_kernel<64>) : go(attention_kernel<64, false>));
     else if (dh == 32)
-        ELIS_TRY(cls_only ? go(attention_kernel<32, true>) : go(attention_kernel<32, false>));
+        ELIS_TRY(cls_only ? go(attention_kernel<32, true>) : narrow ? go(attention_narrow_kernel<32>) : go(attention_kernel<32, false>));
     else
         return hipErrorInvalidValue;
     return hipSuccess;

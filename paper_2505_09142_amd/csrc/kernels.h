@@ -69,6 +69,9 @@ hipError_t launch_gemm_config(int cfg, int group_m, const uint16_t* x, const uin
                               Residual res, int m, int n, int k, int epi, void* out, hipStream_t st);
 void gemm_config_tile(int cfg, int* bm, int* bn, int* wgs_per_cu);
 
+// gemm.hip: compute units of the current device
+int device_cus();
+
 // attention.hip
 // cls_only: only the first query of each sequence, written to row s of out ([n, heads * dh]).
 hipError_t launch_attention(const uint16_t* qkv, SeqTable tab, int n, int total, int heads, int dh,
