@@ -30,7 +30,7 @@ def test_same_bits_alone_and_in_a_large_batch(lens, dh, heads):
     extra = [200] * 500  # more than any threshold of a small launch
     T, D = int(sum(lens)), heads * dh
     gen = torch.Generator(device="cuda").manual_seed(T + dh)
-    qkv = torch.randn((T + sum(extra), 3 * D), generator=gen, device="cuda")
+    qkv = torch.randn((T + sum(extra), 3 * D), generator=gen, device="cuda", dtype=torch.float32)
     qkv[:, :D] *= 4.0  # sharp enough that running maxima move
     qkv = qkv.to(torch.bfloat16)
     alone = attend(qkv, lens, heads, dh)

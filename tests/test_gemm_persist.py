@@ -90,11 +90,11 @@ def test_same_bits_as_small_tiles(m, n, k, epi):
     from tests.gpu_util import note, ok, stream
     note(f"persistent product m={m} n={n} k={k} epi={epi}")
     gen = torch.Generator(device="cuda").manual_seed(m + n + k)
-    x = torch.randn((m, k), generator=gen, device="cuda").to(torch.bfloat16)
-    w = (0.05 * torch.randn((n, k), generator=gen, device="cuda")).to(torch.bfloat16)
-    bias = torch.randn(n, generator=gen, device="cuda")
+    x = torch.randn((m, k), generator=gen, device="cuda", dtype=torch.float32).to(torch.bfloat16)
+    w = (0.05 * torch.randn((n, k), generator=gen, device="cuda", dtype=torch.float32)).to(torch.bfloat16)
+    bias = torch.randn(n, generator=gen, device="cuda", dtype=torch.float32)
     f32 = epi == E.ELIS_EPI_BIAS_RES_F32
-    res = torch.randn((m, n), generator=gen, device="cuda") if f32 else None
+    res = torch.randn((m, n), generator=gen, device="cuda", dtype=torch.float32) if f32 else None
     guard = 4096  # elements past the output that must stay as they are
     outs = []
     for tile in ((256, 256, 1), (128, 128, 2)):
@@ -118,11 +118,11 @@ def test_few_rows_same_bits_as_small_tiles(m, n, k, epi):
     from tests.gpu_util import note, ok, stream
     note(f"few rows m={m} n={n} k={k} epi={epi}")
     gen = torch.Generator(device="cuda").manual_seed(m + n + k)
-    x = torch.randn((m, k), generator=gen, device="cuda").to(torch.bfloat16)
-    w = (0.05 * torch.randn((n, k), generator=gen, device="cuda")).to(torch.bfloat16)
-    bias = torch.randn(n, generator=gen, device="cuda")
+    x = torch.randn((m, k), generator=gen, device="cuda", dtype=torch.float32).to(torch.bfloat16)
+    w = (0.05 * torch.randn((n, k), generator=gen, device="cuda", dtype=torch.float32)).to(torch.bfloat16)
+    bias = torch.randn(n, generator=gen, device="cuda", dtype=torch.float32)
     f32 = epi == E.ELIS_EPI_BIAS_RES_F32
-    res = torch.randn((m, n), generator=gen, device="cuda") if f32 else None
+    res = torch.randn((m, n), generator=gen, device="cuda", dtype=torch.float32) if f32 else None
     outs = []
     for plan in (None, (64, 64, 2, m, 0, 0, 0)):
         out = torch.full((m * n + 4096,), 7.0, dtype=torch.float32 if f32 else torch.bfloat16, device="cuda")
