@@ -129,7 +129,9 @@ def _gemm_kernel(bm, bn, wgs, epi, n, f32):
 def class_kernels(workload: str) -> dict:
     """class -> (kernel names any launch of the class dispatches, sources, launches per pass).
     A GEMM class uses the plan at T rows (one or two kernels) and, with CLS pooling, the plan at
-    n rows in the last layer; the out-projection of that layer also gathers its residual rows."""
+    n rows in the last layer, or 32 x 32 tiles in its place where the library prices them lower (up to
+    512 tiles); the out-projection of that layer also gathers its residual rows. Attention has a narrow
+    form for small launches. A summary counts the names that its run dispatched (_dispatched)."""
     from paper_2505_09142_amd import _elis as E
     from workloads import WORKLOADS, make_batch
     w = WORKLOADS[workload]
@@ -150,16 +152,28 @@ def class_kernels(workload: str) -> dict:
                     [_gemm_kernel(rbm, rbn, rwg, internal, nn, pub == 2)] if m1 < m else []):
                 if kname not in names:
                     names.append(kname)
+            few = f"gemm_wave_kernel<{internal}>"
+            if nn % 128 == 0 and (m + 31) // 32 * (nn // 32) <= 512 and few not in names:
+                names.append(few)
         if cls == "gemm_o" and cls_tail:
             names.append("gather_rows_kernel")
         out[cls] = (names, _GEMM_SRC, L)
     vpl = (d + 255) // 256
-    att = [f"attention_kernel<{d // s.n_heads}, false>"] + ([f"attention_kernel<{d // s.n_heads}, true>"] if cls_tail
+    att = [f"attention_kernel<{d // s.n_heads}, false>", f"attention_narrow_kernel<{d // s.n_heads}>"] + ([f"attention_kernel<{d // s.n_heads}, true>"] if cls_tail
                                                              else [])
     out["attention"] = (att, ["paper_2505_09142_amd/csrc/attention.hip", "paper_2505_09142_amd/csrc/common.h"], L)
     out["layernorm"] = ([f"layernorm_kernel<{vpl}>"], ["paper_2505_09142_amd/csrc/norm.hip",
                                                         "paper_2505_09142_amd/csrc/common.h"], 2 * L)
     return out
+
+
+def _dispatched(names, table):
+    return [k for k in names if table.get(k)]
+
+
+def _passes(table, count=len):
+    """Forward passes in a profile: one sequence-table launch each."""
+    return sum(count(table[k]) for k in ("seqmap_kernel", "seqmap_direct_kernel") if k in table)
 
 
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
@@ -223,7 +237,7 @@ def summarize_pmc(fetch_csv, write_csv, copy_mib, workload, commands):
     mandatory["gemm_qkv"] = T * d * 2 + 3 * d * d * 2 + 3 * d * 4 + qkv_b
     att_tail = (qkv_b * 2 // 3 + n * d * 2 * 2) if cls_tail else qkv_b + T * d * 2
     mandatory["attention"] = ((L - 1) * (qkv_b + T * d * 2) + att_tail) / L
-    passes = len(fetch.get("seqmap_kernel", []))
+    passes = _passes(fetch)
     lines = [f"# HBM traffic per launch: {workload} (T = {T:,}), rocprofv3 PMC byte counters", "",
              "Two passes over the same bench command, one counter each (MI355X, repo root as working tree):", ""]
     lines += [f"    {c}" for c in commands]
@@ -236,9 +250,10 @@ def summarize_pmc(fetch_csv, write_csv, copy_mib, workload, commands):
               "|---|---|---:|---:|---:|---:|---:|---:|"]
     recs = {}
     for cls, (knames, srcs, lpp) in class_kernels(workload).items():
+        knames = _dispatched(knames, fetch)
         label = " + ".join(f"`{k}`" for k in knames)
         fvs, wvs = [fetch.get(k, []) for k in knames], [write.get(k, []) for k in knames]
-        if not passes or not all(fvs) or not all(wvs):
+        if not passes or not fvs or not all(wvs):
             lines.append(f"| {cls} | {label} | 0 | - | - | - | - | - |")
             continue
         # per class launch: every dispatch of the class's kernels over the passes, / launches
@@ -276,7 +291,7 @@ def summarize_mfma(csv_path, bench_json, command):
             n = re.sub(r"\(.*", "", r["Kernel_Name"].replace("elis::(anonymous namespace)::", "").replace("void ", "")).strip()
             vals[n][r["Counter_Name"]].append(float(r["Counter_Value"]))
             durations[n][r["Dispatch_Id"]] = int(r["End_Timestamp"]) - int(r["Start_Timestamp"])
-    passes = len(durations.get("seqmap_kernel", {}))
+    passes = _passes(durations)
     simds, ses = 1024, 32  # MI355X: 256 CUs x 4 SIMDs; 8 XCDs x 4 shader engines
     lines = ["# MFMA busy per kernel: bert_base_b64, rocprofv3 PMC counters", "",
              "Command (MI355X, repo root as working tree):", "", f"    {command}", "",
@@ -289,8 +304,9 @@ def summarize_mfma(csv_path, bench_json, command):
              "| class | kernels | dispatches | MFMA busy | algorithmic | algorithmic / busy |",
              "|---|---|---:|---:|---:|---:|"]
     for cls, (knames, _, per_pass) in class_kernels(rec["config"]["workload"].split(":")[0]).items():
+        knames = _dispatched(knames, vals)
         vs = [vals.get(k) for k in knames]
-        if not all(v and v.get("SQ_VALU_MFMA_BUSY_CYCLES") for v in vs):
+        if not vs or not all(v and v.get("SQ_VALU_MFMA_BUSY_CYCLES") for v in vs):
             continue
         # cycles summed over every dispatch of the class's kernels
         mb = sum(sum(v["SQ_VALU_MFMA_BUSY_CYCLES"]) for v in vs)
@@ -341,8 +357,9 @@ def summarize_issue(csv_path, command):
              "|---|---:|---:|---:|---:|---:|"]
     rec_cls = class_kernels("bert_base_b64")
     for cls, (knames, _, _) in rec_cls.items():
+        knames = _dispatched(knames, vals)
         vs = [vals.get(k) for k in knames]
-        if not all(vs):
+        if not vs:
             continue
         tot = collections.defaultdict(float)
         for v in vs:
@@ -363,8 +380,8 @@ def summarize_issue(csv_path, command):
 
 
 TRACE_PROFILE = os.path.join(ROOT, "profiles", "bert_base_b64_kernel_trace.md")
-_ROLES = {"seqmap_kernel": "sequence table", "embed_ln_kernel<3>": "embedding + LN",
-          "select_rank_kernel": "ISRTF select", "head_tile_kernel<0, true, 8>": "head 768->256 + ReLU (CLS rows)",
+_ROLES = {"seqmap_kernel": "sequence table", "seqmap_direct_kernel": "sequence table", "embed_ln_kernel<3>": "embedding + LN",
+          "select_rank_kernel<16, PlainJobs>": "ISRTF select", "head_tile_kernel<0, true, 8>": "head 768->256 + ReLU (CLS rows)",
           "head_out_kernel": "head 256->1, affine", COPY_KERNEL: "(torch copies)"}
 
 
@@ -387,9 +404,9 @@ def summarize_trace(stats_csv, command, bench_json, plain_json=None):
                         f"{float(r['AverageNs']) / 1e3:.2f} | {float(r['Percentage']):.2f} |")
     rl = rec["roofline"]
     dom = rl["kernel"]
-    passes = calls.get("seqmap_kernel", 0)
+    passes = _passes(calls, int)
     prof_us = (sum(tot.get(k, 0.0) for k in ck[dom][0]) / (passes * ck[dom][2])
-               if dom in ck and passes and all(k in tot for k in ck[dom][0]) else None)
+               if dom in ck and passes and _dispatched(ck[dom][0], tot) else None)
     cfg = rec["config"]
     steps, warm = rec["steps"], rec["warmup"]
     lines = [f"# Kernel trace: {cfg['workload'].split(':')[0]} (T = {cfg['total_tokens']:,}), predict + select", "",
@@ -418,43 +435,41 @@ def summarize_trace(stats_csv, command, bench_json, plain_json=None):
 
 
 SELECT_PROFILE = os.path.join(ROOT, "profiles", "select_large_n.md")
-_SELECT_STAGES = ["init", "count 11b", "reduce", "count 11b", "reduce", "count 10b", "reduce", "scatter", "final"]
-
 
 def summarize_select(sweep_json, trace_csv, command):
-    """Write the large-n select summary: bench.py --select-sweep's line plus per-kernel medians
-    from a rocprofv3 kernel trace of the same command (each call is 9 launches in order)."""
+    """Write the large-n select summary: bench.py --select-sweep's line plus the kernel medians of a call
+    from a rocprofv3 kernel trace of the same command (a call starts with select_init_kernel or select_minima_kernel)."""
     import csv
     import statistics
     rows = json.loads(open(sweep_json).read().strip().splitlines()[-1])["select_sweep"]
     with open(trace_csv) as f:
         tr = sorted((r for r in csv.DictReader(f) if "select_" in r["Kernel_Name"]),
                     key=lambda r: int(r["Start_Timestamp"]))
-    nk = len(_SELECT_STAGES)
-    calls = [tr[i:i + nk] for i in range(0, len(tr), nk)]
+    calls = []
+    for r in tr:
+        name = re.search(r"select_(\w+)_kernel", r["Kernel_Name"]).group(1)
+        if name in ("init", "minima"):
+            calls.append([])
+        calls[-1].append((name, (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3))
     per_cfg = len(calls) // len(rows)
-    lines = ["# ISRTF select above 8192 jobs: device-wide radix selection, n = 2^20 .. 2^24", "",
+    lines = ["# ISRTF select above 8192 jobs: group minima or device-wide radix selection, n = 2^20 .. 2^24", "",
              "Commands (MI355X, repo root as working tree):", "",
              "    python bench.py --select-sweep", f"    {command}", "",
              "Predictions 250 + 100 * N(0, 0.55^2) (the predictor's output scale), arrivals a random "
              "permutation. `mandatory` = 12 n bytes in (pred + arrival) + 4 k out; HBM fraction = "
-             "mandatory bytes / time / 8 TB/s. The implementation reads pred four times (16 n bytes) "
-             "and arrivals only for jobs tied on the prediction.", "",
+             "mandatory bytes / time / 8 TB/s. The radix path reads pred four times (16 n bytes), the group minima "
+             "twice, and both read arrivals only for jobs tied on the prediction.", "",
              "| n | k | µs per call (HIP events) | GB/s of mandatory bytes | HBM fraction |",
              "|---:|---:|---:|---:|---:|"]
     for r in rows:
         lines.append(f"| 2^{r['n'].bit_length() - 1} | {r['k']} | {r['us']:.1f} | {r['gbs']:.0f} | {r['hbm_frac']:.3f} |")
-    lines += ["", "Per-kernel medians from the trace (µs; a stage that finds its bucket already resolved "
-              "returns at once):", "",
-              "| n | k | " + " | ".join(_SELECT_STAGES) + " |", "|---:|---:|" + "---:|" * nk]
+    lines += ["", "Kernels of a call in order, medians from the trace (µs; a pass that finds its bucket already "
+              "resolved returns at once):", "", "| n | k | kernels |", "|---:|---:|---|"]
     for ci, r in enumerate(rows):
-        cs = calls[ci * per_cfg + 3:(ci + 1) * per_cfg]
-        med = [statistics.median((int(c[j]["End_Timestamp"]) - int(c[j]["Start_Timestamp"])) / 1e3 for c in cs)
-               for j in range(nk)]
-        lines.append(f"| 2^{r['n'].bit_length() - 1} | {r['k']} | " + " | ".join(f"{v:.1f}" for v in med) + " |")
-    lines += ["", "Small launches cost 2-5 µs each (nine per call), so below 2^22 jobs the call is "
-              "launch-bound; at k = 8192 the one-work-group bitonic sort of the chosen jobs (~170 µs) "
-              "dominates."]
+        cs = [c for c in calls[ci * per_cfg + 3:(ci + 1) * per_cfg]]
+        cs = [c for c in cs if len(c) == len(cs[0])]
+        med = [f"{cs[0][j][0]} {statistics.median(c[j][1] for c in cs):.1f}" for j in range(len(cs[0]))]
+        lines.append(f"| 2^{r['n'].bit_length() - 1} | {r['k']} | {', '.join(med)} |")
     with open(SELECT_PROFILE, "w") as f:
         f.write("\n".join(lines) + "\n")
     print(f"wrote {SELECT_PROFILE}")
