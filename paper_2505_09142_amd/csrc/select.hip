@@ -30,6 +30,7 @@
 #include <mutex>
 
 #include "kernels.h"
+#include "kth_range.h"
 
 namespace elis {
 
@@ -689,10 +690,11 @@ __global__ __launch_bounds__(kThreads) void select_minima_kernel(const float* __
 }
 
 // Scratch of block_kth.
+static_assert(kKthBins == kThreads, "one bin per thread");
 struct KthScratch {
     uint32_t range[2][kThreads / kWave];
     int wave[kThreads / kWave];
-    int bin[kThreads];
+    int bin[kKthBins];
     int found, below;
 };
 
@@ -725,13 +727,14 @@ __device__ __forceinline__ uint32_t block_kth(const uint32_t (&v)[PER], bool (&a
         lo = sh.range[0][w] < lo ? sh.range[0][w] : lo;
         hi = sh.range[1][w] > hi ? sh.range[1][w] : hi;
     }
+    KthRange range{lo, hi};
     for (;;) {  // uniform: 32 bits are gone after four rounds
-        const int bits = hi > lo ? 32 - __builtin_clz(hi - lo) : 0, shift = bits > 10 ? bits - 10 : 0;
+        const int shift = range.shift();
         sh.bin[tid] = 0;
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < PER; ++q)
-            if (act[q]) atomicAdd(&sh.bin[(v[q] - lo) >> shift], 1);
+            if (act[q]) atomicAdd(&sh.bin[range.part(v[q], shift)], 1);
         __syncthreads();
         const int mine = sh.bin[tid];
         int incl = mine;
@@ -752,11 +755,9 @@ __device__ __forceinline__ uint32_t block_kth(const uint32_t (&v)[PER], bool (&a
         need -= sh.below;
         active = sh.bin[bin];
 #pragma unroll
-        for (int q = 0; q < PER; ++q) act[q] = act[q] && ((v[q] - lo) >> shift) == bin;
-        lo += bin << shift;
-        if (shift == 0) return lo;
-        const uint32_t top = lo + ((1u << shift) - 1u);
-        hi = top < hi ? top : hi;
+        for (int q = 0; q < PER; ++q) act[q] = act[q] && range.part(v[q], shift) == bin;
+        range.cut(bin, shift);
+        if (shift == 0) return range.lo;
         __syncthreads();  // bins are cleared again
     }
 }

@@ -3,7 +3,8 @@
 Up to 8,192 jobs are ranked directly; above, the candidates come from group minima while at most
 32,768 of them are possible (and at most half of the groups hold any), else from the radix selection. The data are the ones that these bounds depend on:
 in order, in reverse, all smallest jobs in few groups (every 4,096th job: the worst case), few
-distinct keys, one key (so that arrival and index decide), and NaN of both signs with infinities.
+distinct keys, one key (so that arrival and index decide, the arrivals over the whole range of their words too), NaN of
+both signs with infinities, and NaN for all but a few jobs (the bound on the candidates is a NaN beside finite minima).
 """
 import numpy as np
 import pytest
@@ -29,6 +30,14 @@ def data(kind, n, rng):
         return rng.integers(0, 3, size=n).astype(np.float32), arr
     if kind == "one":
         return np.full(n, -3.5, np.float32), rng.integers(-n, n, size=n).astype(np.int64) << 33
+    if kind == "mostly_nan":  # fewer finite keys than are chosen, so that the bound on the candidates is a NaN
+        p = np.full(n, np.nan, np.float32)
+        p[rng.choice(n, 10, replace=False)] = rng.normal(250.0, 100.0, 10)
+        return p, arr
+    if kind == "wide_arrivals":  # one key, arrivals over all values of the low word
+        return np.zeros(n, np.float32), rng.integers(0, 1 << 32, size=n, dtype=np.int64)
+    if kind == "full_arrivals":  # and over all of 64 bits
+        return np.zeros(n, np.float32), rng.integers(-(1 << 63), (1 << 63) - 1, size=n, dtype=np.int64)
     bits = np.array([0x7FC00000, 0xFFC00001, 0x7F800000, 0xFF800000, 0x80000000, 0x00000000, 0x7F7FFFFF], np.uint32)
     return rng.choice(bits, size=n).view(np.float32), arr
 
@@ -41,9 +50,9 @@ def order(pred, arr):
     return np.lexsort((np.arange(len(pred)), arr, key))
 
 
-@pytest.mark.parametrize("kind", ["ascending", "descending", "clustered", "few", "one", "special"])
+@pytest.mark.parametrize("kind", ["ascending", "descending", "clustered", "few", "one", "special", "mostly_nan", "wide_arrivals", "full_arrivals"])
 @pytest.mark.parametrize("n,ks", [(15, (0, 1, 15)), (1025, (1, 1025)), (4096, (64, 4096)), (4097, (64, 5000)), (8192, (63, 8192)),
-                                  (8193, (1, 8192)), (12288, (64, 8192)), (12289, (8192,)), (24576, (8192,)), (32768, (1, 2048, 2049)), (32769, (64, 1024, 1025)),
+                                  (8193, (1, 8192)), (12288, (64, 8192)), (12289, (8192,)), (20000, (64, 1024)), (24576, (8192,)), (32768, (1, 2048, 2049)), (32769, (64, 1024, 1025)),
                                   (262145, (64, 256, 257, 512)), ((1 << 20) - 3, (64, 128, 129)), ((1 << 20) + 5, (64, 65)), (1 << 21, (1, 32, 64, 65)), ((1 << 21) + 1, (64,))])
 def test_select_at_the_edges(n, ks, kind):
     rng = np.random.default_rng(n + len(kind))
