@@ -147,8 +147,8 @@ int32_t elis_select_max_n(void);
 
 /*
  * Largest min(batch_cap, n) accepted for n jobs (0 if n is invalid): unbounded
- * (INT32_MAX) for n <= 8192, where every job is ranked; 8192 above, where the
- * chosen jobs are ranked after a device-wide selection.
+ * (INT32_MAX) for n <= 8192, where every job may be chosen; 8192 above, where the
+ * chosen jobs are put in order by one ranking launch.
  */
 int32_t elis_select_max_batch_cap(int32_t n);
 

@@ -6,8 +6,9 @@
 //   * the float is mapped to an unsigned integer whose order is the float
 //     order, with -0 folded onto +0 and every NaN mapped to the maximum (after
 //     +inf), so the comparison is exact integer work with no rounding;
-//   * n <= 8192: every work-group ranks a few jobs by counting the keys below
-//     theirs (all keys in LDS), and the job of rank r < k lands in out_idx[r];
+//   * n <= 8192, and up to 12288 where k is a large part of n: every work-group
+//     ranks a few jobs by counting the keys below theirs (all keys in LDS), and
+//     the job of rank r < k lands in out_idx[r];
 //   * larger n (k <= 8192), where the smallest jobs of some groups bound the number of
 //     candidates (see "group minima"): three launches;
 //   * else radix selection over the whole device, most
@@ -37,8 +38,8 @@ namespace elis {
 namespace {
 
 constexpr int kThreads = 1024;
-constexpr int kRankMaxN = 8192;  // most jobs of one ranking launch
-constexpr int kSortMaxN = 8192;  // most jobs of one LDS sort
+constexpr int kRankMaxN = 12288;  // most jobs of one ranking launch
+constexpr int kSortMaxN = 8192;   // most jobs of one LDS sort, and most that are always ranked directly
 
 __device__ __forceinline__ uint32_t order_key(float f) {
     uint32_t u = __float_as_uint(f);
@@ -87,7 +88,7 @@ struct TableJobs {
     }
 };
 
-// Ranks a work-group's J jobs among all n <= 8192 and writes those of rank below k. Every
+// Ranks a work-group's J jobs among all n <= 1024 PER and writes those of rank below k. Every
 // work-group holds all n float keys in LDS; a thread counts, for one of the J jobs, the smaller
 // keys of its slice of them (16 bytes per LDS read, two instructions per key). Only a job with
 // fewer than k smaller keys can be chosen: a wave looks through the keys equal to its own and
@@ -95,13 +96,13 @@ struct TableJobs {
 // Bound by launch and load latency up to about 2,000 jobs, then by the counting. It replaces one
 // work-group that ranked up to 1,024 jobs by full comparisons and sorted up to 8,192 in LDS:
 // 256 jobs 12 -> 3.8 us, 1,024 jobs 64 -> 4, 4,096 jobs 74 -> 5.5, 8,192 jobs 151 -> 11 (k = 64).
-template <int J, class Jobs>
+// PER: keys a thread loads, all in flight together.
+template <int J, int PER, class Jobs>
 __global__ __launch_bounds__(kThreads) void select_rank_kernel(Jobs jobs, int n, int k, int32_t* __restrict__ out_idx,
                                                                int32_t* __restrict__ out_count,
                                                                uint32_t* __restrict__ status) {
-    __shared__ __attribute__((aligned(16))) uint32_t sk[kRankMaxN];
+    __shared__ __attribute__((aligned(16))) uint32_t sk[kThreads * PER];
     __shared__ int part[kThreads / kWave][J];
-    constexpr int PER = J == 16 ? 4 : 8;  // keys a thread loads, all in flight together: n <= 1024 PER
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     const int n4 = (n + 3) / 4, i0 = blockIdx.x * J;
     float f[PER];
@@ -169,10 +170,12 @@ template <class Jobs>
 hipError_t launch_rank(const Jobs& jobs, int n, int k, int32_t* out_idx, int32_t* out_count, uint32_t* status,
                        hipStream_t st) {
     // 16 jobs per work-group keep all 256 CUs busy up to 4,096 jobs; above, 32 halve the keys read per job.
-    const dim3 block(kThreads);
-    if (n <= 4096)
-        return launch_kernel(select_rank_kernel<16, Jobs>, dim3((n + 15) / 16), block, 0, st, jobs, n, k, out_idx, out_count, status);
-    return launch_kernel(select_rank_kernel<32, Jobs>, dim3((n + 31) / 32), block, 0, st, jobs, n, k, out_idx, out_count, status);
+    auto go = [&](auto kernel, int j) {
+        return launch_kernel(kernel, dim3((n + j - 1) / j), dim3(kThreads), 0, st, jobs, n, k, out_idx, out_count, status);
+    };
+    if (n <= 4096) return go(select_rank_kernel<16, 4, Jobs>, 16);
+    if (n <= 8192) return go(select_rank_kernel<32, 8, Jobs>, 32);
+    return go(select_rank_kernel<32, kRankMaxN / kThreads, Jobs>, 32);
 }
 
 // ------------------------------------------------------------------------------ large n
@@ -633,10 +636,11 @@ struct ListedJobs {
 //   rank list  the candidates are ranked as in select_rank_kernel.
 // The radix path takes nine launches and four reads of the keys: 45 us at 2^20 jobs, k = 64, this one
 // 20 (4.5 + 9 + 6: launches, load latency and the barriers of the search; the keys are 4 MB).
+// Equal keys cost the ranking a load of the index and one of the arrival per pair: up to 0.8 ms where all
+// of the most candidates tie.
 constexpr int kMinWgs = 256, kMinGroups = 16;  // work-groups, and groups of each
 constexpr int kCandidates = 32768;             // most candidates: their keys are ranked out of LDS
 constexpr int kMinMaxN = 1 << 21;
-constexpr int kMinAllN = 12288;                // every job may be a candidate up to here
 
 struct MinimaWs {
     uint32_t* key;    // [kMinWgs * kMinGroups] minima: ordered key and index (no job: the largest key, index -1)
@@ -910,16 +914,20 @@ __global__ __launch_bounds__(kThreads) void select_rank_list_kernel(const int64_
             for (int q = lane; q < n4; q += kWave) {
                 const uint4 v = s4[q];
                 const uint32_t e[4] = {v.x, v.y, v.z, v.w};
-                if ((v.x == kr) | (v.y == kr) | (v.z == kr) | (v.w == kr)) {
+                uint32_t same = 0;
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const int j = 4 * q + c;
-                        if (e[c] == kr && j != r && j < total) {
-                            const int32_t ij = ws.cidx[place(j)];
-                            const int64_t ar = arrival[ir], aj = arrival[ij];
-                            ties += static_cast<int>((aj < ar) | ((aj == ar) & (ij < ir)));
-                        }
-                    }
+                for (int c = 0; c < 4; ++c) same |= e[c] == kr && 4 * q + c != r && 4 * q + c < total ? 1u << c : 0u;
+                if (!same) continue;
+                const int64_t ar = arrival[ir];
+                int g = find_group(off, kMinWgs, static_cast<uint32_t>(4 * q));  // of the first; the others follow it
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int j = 4 * q + c;
+                    if (!((same >> c) & 1u)) continue;
+                    while (g + 1 < kMinWgs && off[g + 1] <= static_cast<uint32_t>(j)) ++g;
+                    const int32_t ij = ws.cidx[static_cast<size_t>(g) * ws.cap + (j - static_cast<int>(off[g]))];
+                    const int64_t aj = arrival[ij];
+                    ties += static_cast<int>((aj < ar) | ((aj == ar) & (ij < ir)));
                 }
             }
 #pragma unroll
@@ -1010,17 +1018,25 @@ hipError_t launch_select(const float* pred, const int64_t* arrival, int n, int k
                          int32_t* out_count, void* workspace, hipStream_t st) {
     if (n < 1 || n > kLargeMaxN || k < 0) return hipErrorInvalidValue;
     uint32_t* status = static_cast<uint32_t*>(workspace);
-    if (n <= kRankMaxN) return launch_rank(PlainJobs{pred, arrival, nullptr}, n, k, out_idx, out_count, status, st);
+    const PlainJobs all{pred, arrival, nullptr};
+    if (n <= kSortMaxN) return launch_rank(all, n, k, out_idx, out_count, status, st);
     const int kk = k < n ? k : n;
     if (kk > kSortMaxN) return hipErrorInvalidValue;
     // Group minima while the candidates (k groups of at most lanes * 4 * sweeps jobs) fit the ranking kernel's LDS
-    // and at most half of the groups hold any (beyond, nearly every job becomes one), or where all jobs are few.
-    // This path against the radix path in us: 8,193 jobs 18 / 40 (k = 64) and 32 / 48 (k = 4,096); 20,000 jobs
-    // 18 / 40 (k = 64), 89 / 46 (k = 4,096, all of them candidates); 2^20 jobs 20 / 45 (k = 64).
+    // and at most half of the groups hold any (beyond, nearly every job becomes one). Past that, up to 12,288 jobs are
+    // ranked directly, more take the radix path. In us, distinct keys / one key for all jobs (FCFS):
+    //                        minima       direct       radix
+    //   8,193, k = 64       18 / 54        -          39 / 199
+    //   8,193, k = 2,048    34 / 263    15 / 69       70 / 222
+    //   12,288, k = 8,192   47 / 539    30 / 186     187 / 375
+    //   65,536, k = 1,024   21 / 809       -          55 / 981
+    //   2^20, k = 64        21 / 80        -          45 / 17,000
     MinimaWs mw;
     const bool fits = minima_layout(n, &mw, static_cast<char*>(workspace)) <= large_layout(n, nullptr, nullptr);
     const int most = kk * (mw.lanes * 4 * mw.sweeps);
-    if (kk > 0 && n <= kMinMaxN && fits && (n <= kMinAllN || (most <= kCandidates && 2 * most <= n))) {
+    const bool few = 2 * most <= n;
+    if (n <= kRankMaxN && !few) return launch_rank(all, n, kk, out_idx, out_count, status, st);
+    if (kk > 0 && n <= kMinMaxN && fits && few && most <= kCandidates) {
         ELIS_TRY(launch_kernel(select_minima_kernel, dim3(kMinWgs), dim3(kThreads), 0, st, pred, arrival, n, mw));
         ELIS_TRY(launch_kernel(select_filter_kernel, dim3(kMinWgs), dim3(kThreads), 0, st, pred, arrival, n, kk, mw));
         ELIS_TRY(launch_kernel(select_rank_list_kernel, dim3(kMinWgs), dim3(kThreads), 0, st, arrival, kk, mw, out_idx, out_count,
@@ -1056,7 +1072,7 @@ hipError_t launch_jobs_select(JobTable t, const int32_t* slots, const float* wai
     void* sel_ws = p + align_up(4 * n) + align_up(8 * n) + align_up(4 * n);
     // Bad slots are flagged in the table's status word: the select clears its own.
     ELIS_TRY(launch_jobs_gather(t, slots, wait, aging, a, pred, arr, st));
-    if (a <= kRankMaxN)
+    if (a <= kSortMaxN)
         return launch_rank(PlainJobs{pred, arr, slots}, a, k, out_slots, out_count, static_cast<uint32_t*>(sel_ws), st);
     ELIS_TRY(launch_select(pred, arr, a, k, idx, out_count, sel_ws, st));
     const int kk = k < a ? k : a;

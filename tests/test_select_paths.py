@@ -1,7 +1,8 @@
 """Selection where its launch paths meet and where their bounds are reached, against the sort-based oracle.
 
 Up to 8,192 jobs are ranked directly; above, the candidates come from group minima while at most
-32,768 of them are possible (and at most half of the groups hold any), else from the radix selection. The data are the ones that these bounds depend on:
+32,768 of them are possible and at most half of the groups hold any (8,193 jobs: k = 1,024, 12,288 jobs: k = 1,536).
+Past that, up to 12,288 jobs are ranked directly too, more of them go through the radix selection. The data are the ones that these bounds depend on:
 in order, in reverse, all smallest jobs in few groups (every 4,096th job: the worst case), few
 distinct keys, one key (so that arrival and index decide, the arrivals over the whole range of their words too), NaN of
 both signs with infinities, and NaN for all but a few jobs (the bound on the candidates is a NaN beside finite minima).
@@ -52,7 +53,7 @@ def order(pred, arr):
 
 @pytest.mark.parametrize("kind", ["ascending", "descending", "clustered", "few", "one", "special", "mostly_nan", "wide_arrivals", "full_arrivals"])
 @pytest.mark.parametrize("n,ks", [(15, (0, 1, 15)), (1025, (1, 1025)), (4096, (64, 4096)), (4097, (64, 5000)), (8192, (63, 8192)),
-                                  (8193, (1, 8192)), (12288, (64, 8192)), (12289, (8192,)), (20000, (64, 1024)), (24576, (8192,)), (32768, (1, 2048, 2049)), (32769, (64, 1024, 1025)),
+                                  (8193, (1, 1024, 1025, 8192)), (12288, (64, 1536, 1537, 8192)), (12289, (8192,)), (20000, (64, 1024)), (24576, (8192,)), (32768, (1, 2048, 2049)), (32769, (64, 1024, 1025)),
                                   (262145, (64, 256, 257, 512)), ((1 << 20) - 3, (64, 128, 129)), ((1 << 20) + 5, (64, 65)), (1 << 21, (1, 32, 64, 65)), ((1 << 21) + 1, (64,))])
 def test_select_at_the_edges(n, ks, kind):
     rng = np.random.default_rng(n + len(kind))
