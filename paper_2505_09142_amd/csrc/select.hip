@@ -166,6 +166,45 @@ __global__ __launch_bounds__(kThreads) void select_rank_kernel(Jobs jobs, int n,
     }
 }
 
+// Ranks up to 64 jobs. Every wave holds all of them, one per lane, and takes four in turn: the jobs before
+// one are the set bits of one comparison over the wave. No LDS and no barrier, so that what remains is the
+// launch and one load: 2 to 32 jobs 1.8 us, 64 jobs 2.0, whatever ties (the counting kernel above 2.4 to 2.75 with
+// distinct keys and up to 3.5 with equal ones, the loop over LDS before it 1.8 for 2 jobs, 2.8 for 32).
+constexpr int kFewMaxN = kWave, kFewPerWave = 4;
+template <class Jobs>
+__global__ __launch_bounds__(kFewMaxN / kFewPerWave* kWave) void select_few_kernel(Jobs jobs, int n, int k,
+                                                                                   int32_t* __restrict__ out_idx,
+                                                                                   int32_t* __restrict__ out_count,
+                                                                                   uint32_t* __restrict__ status) {
+    const int j = threadIdx.x & (kWave - 1), first = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) * kFewPerWave;
+    uint32_t kj = 0u;
+    int64_t aj = 0;
+    int32_t cj = 0;
+    if (j < n) {
+        cj = jobs.chosen(j);
+        aj = jobs.arrived(j);
+        kj = order_key(jobs.key(j));
+        if (first == 0) jobs.check(j);
+    }
+    const int lo = static_cast<int>(aj), hi = static_cast<int>(aj >> 32);
+    int mine = INT_MAX;  // rank of this lane's job, where this wave ranks it
+#pragma unroll
+    for (int r = 0; r < kFewPerWave; ++r) {
+        const int i = first + r;
+        const uint32_t ki = __builtin_amdgcn_readlane(kj, i);
+        const int64_t ai = static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(hi, i))) << 32 |
+                                                static_cast<uint32_t>(__builtin_amdgcn_readlane(lo, i)));
+        const bool before = (j < n) & ((kj < ki) | ((kj == ki) & ((aj < ai) | ((aj == ai) & (j < i)))));
+        const int rank = __builtin_popcountll(__builtin_amdgcn_ballot_w64(before));
+        mine = j == i ? rank : mine;
+    }
+    if (j < n && mine < k) out_idx[mine] = cj;
+    if (threadIdx.x == 0) {
+        *out_count = k < n ? k : n;
+        if (status) *status = 0u;
+    }
+}
+
 template <class Jobs>
 hipError_t launch_rank(const Jobs& jobs, int n, int k, int32_t* out_idx, int32_t* out_count, uint32_t* status,
                        hipStream_t st) {
@@ -173,6 +212,9 @@ hipError_t launch_rank(const Jobs& jobs, int n, int k, int32_t* out_idx, int32_t
     auto go = [&](auto kernel, int j) {
         return launch_kernel(kernel, dim3((n + j - 1) / j), dim3(kThreads), 0, st, jobs, n, k, out_idx, out_count, status);
     };
+    if (n <= kFewMaxN)
+        return launch_kernel(select_few_kernel<Jobs>, dim3(1), dim3((n + kFewPerWave - 1) / kFewPerWave * kWave), 0, st, jobs, n, k,
+                             out_idx, out_count, status);
     if (n <= 4096) return go(select_rank_kernel<16, 4, Jobs>, 16);
     if (n <= 8192) return go(select_rank_kernel<32, 8, Jobs>, 32);
     return go(select_rank_kernel<32, kRankMaxN / kThreads, Jobs>, 32);

@@ -47,7 +47,7 @@ def test_append_and_pack(n, max_pos):
 
 
 @pytest.mark.parametrize("aging", [None, 10.0])
-@pytest.mark.parametrize("a", [1, 16, 17, 1023, 1024, 1025, 4096, 4097, 8192, 8193, 20001])
+@pytest.mark.parametrize("a", [1, 16, 17, 63, 64, 65, 1023, 1024, 1025, 4096, 4097, 8192, 8193, 20001])
 def test_select_over_the_table(a, aging):
     note(f"jobs select a={a} aging={aging}")
     rng = np.random.default_rng(a)
@@ -74,7 +74,7 @@ def test_select_over_the_table(a, aging):
     assert t.status() == (E.ELIS_OK, 0)
 
 
-@pytest.mark.parametrize("a", [3, 2000])
+@pytest.mark.parametrize("a", [3, 64, 65, 2000])
 def test_bad_slots_are_flagged_and_rank_last(a):
     note(f"jobs select with a bad slot a={a}")
     t = JobTable(a, 4)

@@ -1,6 +1,6 @@
 """Selection where its launch paths meet and where their bounds are reached, against the sort-based oracle.
 
-Up to 8,192 jobs are ranked directly; above, the candidates come from group minima while at most
+Up to 64 jobs are ranked in one work-group, up to 8,192 by the counting kernel; above, the candidates come from group minima while at most
 32,768 of them are possible and at most half of the groups hold any (8,193 jobs: k = 1,024, 12,288 jobs: k = 1,536).
 Past that, up to 12,288 jobs are ranked directly too, more of them go through the radix selection. The data are the ones that these bounds depend on:
 in order, in reverse, all smallest jobs in few groups (every 4,096th job: the worst case), few
@@ -33,7 +33,7 @@ def data(kind, n, rng):
         return np.full(n, -3.5, np.float32), rng.integers(-n, n, size=n).astype(np.int64) << 33
     if kind == "mostly_nan":  # fewer finite keys than are chosen, so that the bound on the candidates is a NaN
         p = np.full(n, np.nan, np.float32)
-        p[rng.choice(n, 10, replace=False)] = rng.normal(250.0, 100.0, 10)
+        p[rng.choice(n, min(n, 10), replace=False)] = rng.normal(250.0, 100.0, min(n, 10))
         return p, arr
     if kind == "wide_arrivals":  # one key, arrivals over all values of the low word
         return np.zeros(n, np.float32), rng.integers(0, 1 << 32, size=n, dtype=np.int64)
@@ -52,7 +52,7 @@ def order(pred, arr):
 
 
 @pytest.mark.parametrize("kind", ["ascending", "descending", "clustered", "few", "one", "special", "mostly_nan", "wide_arrivals", "full_arrivals"])
-@pytest.mark.parametrize("n,ks", [(15, (0, 1, 15)), (1025, (1, 1025)), (4096, (64, 4096)), (4097, (64, 5000)), (8192, (63, 8192)),
+@pytest.mark.parametrize("n,ks", [(1, (0, 1, 3)), (15, (0, 1, 15)), (63, (1, 63)), (64, (5, 64)), (65, (5, 65)), (1025, (1, 1025)), (4096, (64, 4096)), (4097, (64, 5000)), (8192, (63, 8192)),
                                   (8193, (1, 1024, 1025, 8192)), (12288, (64, 1536, 1537, 8192)), (12289, (8192,)), (20000, (64, 1024)), (24576, (8192,)), (32768, (1, 2048, 2049)), (32769, (64, 1024, 1025)),
                                   (262145, (64, 256, 257, 512)), ((1 << 20) - 3, (64, 128, 129)), ((1 << 20) + 5, (64, 65)), (1 << 21, (1, 32, 64, 65)), ((1 << 21) + 1, (64,))])
 def test_select_at_the_edges(n, ks, kind):
