@@ -1,6 +1,7 @@
 """The job table where its launches change: packs at and past 1,024 jobs (one launch or two), selects that
 gather by themselves (up to 1,024 candidates), rank a gathered list (8,192) and select over the device,
-and appends that wrap the ring, start a job, or carry nothing; against plain numpy."""
+and appends that wrap the ring, start a job, or carry nothing, by work-groups and (past 8,192 jobs of few tokens)
+by tokens; against plain numpy."""
 import numpy as np
 import pytest
 import torch
@@ -17,7 +18,7 @@ def expected_input(tokens, max_pos):
 
 
 @pytest.mark.parametrize("max_pos", [2, 16, 33])
-@pytest.mark.parametrize("n", [1, 255, 256, 257, 1023, 1024, 1025, 2049])
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 1023, 1024, 1025, 2049, 8192, 8193])
 def test_append_and_pack(n, max_pos):
     note(f"jobs append + pack n={n} max_pos={max_pos}")
     rng = np.random.default_rng(n + max_pos)
