@@ -181,9 +181,10 @@ __global__ __launch_bounds__(kThreads) void jobs_pack_gather_kernel(JobTable t, 
 }
 
 // Both at once for up to kPackFused jobs: every work-group scans the lengths itself (one per thread) and
-// gathers kPackTokens of the output; the first one writes cu and reports. The scan costs less than
-// a second launch that waits for the first (64 jobs: 2.9 + 4.2 us and the gap between them -> 4.3 us).
-constexpr int kPackFused = 1024, kPackTokens = 2048;
+// gathers two tokens of the output per thread (more would be fetched one after the other: eight took 8.1 us for 64
+// jobs); the first one writes cu and reports. The scan costs less than a second launch that waits for
+// the first: 64 jobs 6.4 -> 3.9 us, 1,024 jobs of 512 tokens 8.9 -> 5.6.
+constexpr int kPackFused = 1024, kPackPerThread = 2;
 __global__ __launch_bounds__(kPackFused) void jobs_pack_kernel(JobTable t, const int32_t* __restrict__ slots, int n,
                                                                int total, int max_seqlen, int32_t* __restrict__ cu,
                                                                int32_t* __restrict__ ids) {
@@ -228,7 +229,10 @@ __global__ __launch_bounds__(kPackFused) void jobs_pack_kernel(JobTable t, const
         if (bad) atomicOr(t.status, bad);
     }
     const int R = t.max_pos - 1;
-    for (int q = blockIdx.x * kPackTokens + i; q < total && q < (blockIdx.x + 1) * kPackTokens; q += static_cast<int>(blockDim.x)) {
+    for (int u = 0; u < kPackPerThread; ++u) {
+        const long long at_q = (static_cast<long long>(blockIdx.x) * kPackPerThread + u) * blockDim.x + i;
+        if (at_q >= total) break;
+        const int q = static_cast<int>(at_q);
         const int sq = find_segment(cs, n, q);
         const int32_t s = ss[sq];
         const int at = q - cs[sq], len = lens[sq];
@@ -339,9 +343,9 @@ hipError_t launch_jobs_append(JobTable t, const int32_t* slots, const int32_t* o
 hipError_t launch_jobs_pack(JobTable t, const int32_t* slots, int n, int total, int max_seqlen, int32_t* ids,
                             int32_t* cu, hipStream_t st) {
     if (n <= kPackFused) {
-        const int threads = n <= 256 ? 256 : kPackFused;
-        return launch_kernel(jobs_pack_kernel, dim3((total + kPackTokens - 1) / kPackTokens), dim3(threads), 0, st, t, slots,
-                             n, total, max_seqlen, cu, ids);
+        const int threads = n <= 256 ? 256 : kPackFused, per_wg = kPackPerThread * threads;
+        const unsigned wgs = static_cast<unsigned>((static_cast<long long>(total) + per_wg - 1) / per_wg);
+        return launch_kernel(jobs_pack_kernel, dim3(wgs), dim3(threads), 0, st, t, slots, n, total, max_seqlen, cu, ids);
     }
     ELIS_TRY(launch_kernel(jobs_pack_scan_kernel, dim3(1), dim3(1024), 0, st, t, slots, n, total, max_seqlen, cu));
     ELIS_TRY(launch_kernel(jobs_pack_gather_kernel, grid_for(total), dim3(kThreads), 0, st, t, slots, n, total, cu, ids));
