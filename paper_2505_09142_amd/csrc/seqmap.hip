@@ -39,7 +39,8 @@ __device__ __forceinline__ int wave_incl_scan(int v, int lane) {
 // Up to kDirect sequences: every sequence counts the tiles listed before its own (and before it in the
 // batch), 1,024 / p2 threads sharing the count (p2 = n rounded up to a power of two): two barriers and one round
 // of loads, where the chunked kernel below scans, then walks a wave's 64 sequences one by one.
-// Bound by launch and load latency: 64 sequences 8.0 -> 5.3 us.
+// Bound by launch and load latency (map and one-head attention of 64 short sequences 10.0 -> 5.4 us), past 64 sequences
+// by the counting (128: 10.2 -> 6.2, 256: 10.5 -> 9.5).
 __global__ __launch_bounds__(kThreads) void seqmap_direct_kernel(const int32_t* __restrict__ cu, int n, int total,
                                                                  int max_seqlen, int32_t* __restrict__ start,
                                                                  int32_t* __restrict__ len,
@@ -83,7 +84,8 @@ __global__ __launch_bounds__(kThreads) void seqmap_direct_kernel(const int32_t* 
     if (s < n && first < n) {
         const int b = item[s].x;
         int l = 0, q = 0, all = 0;
-        for (int j = first; j < n; j += step) {
+#pragma unroll 8
+        for (int j = first; j < n; j += step) {  // reads of several in flight: each waits for LDS
             const int ob = item[j].x, ot = item[j].y;
             all += ot;
             q += j < s ? ot : 0;
@@ -233,7 +235,9 @@ __global__ __launch_bounds__(kThreads) void seqmap_kernel(const int32_t* __restr
 
 hipError_t launch_seqmap(const int32_t* cu, int n, int total, int max_seqlen, SeqTable tab, uint32_t* status,
                          hipStream_t st) {
-    if (n <= kDirect)
+    // Without a work list the chunked kernel has nothing to walk and only scans: map and linear head of 64 sequences
+    // 5.35 us by chunks and 5.1 directly, 96 sequences 5.2 and 5.5, 256 sequences 5.3 and 8.8.
+    if (n <= (tab.work ? kDirect : kWave))
         return launch_kernel(seqmap_direct_kernel, dim3(1), dim3(kThreads), 0, st, cu, n, total, max_seqlen, tab.start,
                              tab.len, tab.tile_off, tab.work, attn_work_capacity(n, total), status);
     ELIS_TRY(launch_kernel(seqmap_kernel, dim3(1), dim3(kThreads), 0, st, cu, n, total, max_seqlen, tab.start,
