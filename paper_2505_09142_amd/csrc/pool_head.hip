@@ -147,21 +147,21 @@ __global__ __launch_bounds__(kWave) void head_fc_kernel(const float* __restrict_
 // summed through LDS in wave order, the bias added and the activation applied by wave 0.
 // Every output depends on its own sequence's row only, in a fixed order: results do not depend
 // on how many sequences are batched. grid (N / 16, ceil(n / 16)), NW waves; K % (16 NW) == 0.
-template <int ACT, bool POOLED, int NW>
+// BATCH: steps of 16 inputs in LDS at once, 2 NW KB of LDS each.
+template <int ACT, bool POOLED, int NW, int BATCH>
 __global__ __launch_bounds__(NW* kWave) void head_tile_kernel(const float* __restrict__ in,
                                                               const float* __restrict__ hidden,
                                                               const float* __restrict__ z,
                                                               const int32_t* __restrict__ start, int pooling, int n,
                                                               int K, int N, const float* __restrict__ w,
                                                               const float* __restrict__ b, float* __restrict__ out) {
-    // Up to kBatch steps of 16 inputs per pass, all requested before the first block (a wave's share of K is
+    // Up to BATCH steps of 16 inputs per pass, all requested before the first block (a wave's share of K is
     // short, so the pass is bound by one load latency, not by a chain). A step is 16 rows x 64 bytes of each
     // operand, loaded straight into the wave's own LDS: four lanes fetch a row's 64 bytes, so a load touches 16
     // lines, where loading the block's operands (one row per lane) cost a cache access per lane, 8,192 a
-    // work-group: a 1,024 x 1,024 layer of 64 sequences 7.1 -> 5.4 us. 16-byte units are XOR-swizzled by groups of four rows, which keeps
-    // the operand reads free of bank conflicts.
-    constexpr int kBatch = 8;
-    __shared__ __attribute__((aligned(1024))) float stage[NW][kBatch][2][16 * 16];
+    // work-group: a 1,024 x 1,024 layer of 64 sequences 7.1 -> 5.4 us. 16-byte units are XOR-swizzled by groups
+    // of four rows, which keeps the operand reads free of bank conflicts.
+    __shared__ __attribute__((aligned(1024))) float stage[NW][BATCH][2][16 * 16];
     __shared__ f32x4 part[NW][kWave];
     const int o0 = blockIdx.x * 16, s0 = blockIdx.y * 16;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -201,10 +201,13 @@ __global__ __launch_bounds__(NW* kWave) void head_tile_kernel(const float* __res
         asm volatile("" ::: "memory");
     };
     int m0 = 0;
-    for (; m0 + kBatch <= steps; m0 += kBatch) pass(m0, std::integral_constant<int, kBatch>());
-    if (m0 + 4 <= steps) pass(m0, std::integral_constant<int, 4>()), m0 += 4;
-    if (m0 + 2 <= steps) pass(m0, std::integral_constant<int, 2>()), m0 += 2;
-    if (m0 < steps) pass(m0, std::integral_constant<int, 1>());
+    for (; m0 + BATCH <= steps; m0 += BATCH) pass(m0, std::integral_constant<int, BATCH>());
+    if constexpr (BATCH > 4)
+        if (m0 + 4 <= steps) pass(m0, std::integral_constant<int, 4>()), m0 += 4;
+    if constexpr (BATCH > 2)
+        if (m0 + 2 <= steps) pass(m0, std::integral_constant<int, 2>()), m0 += 2;
+    if constexpr (BATCH > 1)
+        if (m0 < steps) pass(m0, std::integral_constant<int, 1>());
     part[wv][lane] = acc;
     __syncthreads();
     if (wv != 0) return;
@@ -252,20 +255,28 @@ __global__ __launch_bounds__(kWave) void head_out_kernel(const float* __restrict
 
 namespace {
 
+template <int ACT, bool POOLED, int NW>
+hipError_t fc_tile(const float* in, const float* hidden, const float* z, const int32_t* start, int pooling, int n, int K,
+                   int N, const float* w, const float* b, float* out, hipStream_t st) {
+    auto go = [&](auto kernel) {
+        return launch_kernel(kernel, dim3(N / 16, (n + 15) / 16), dim3(NW * kWave), 0, st, in, hidden, z, start, pooling, n, K, N, w,
+                             b, out);
+    };
+    // LDS for the steps a wave has, no more: with room for eight of them a CU holds one work-group whatever the depth.
+    const int steps = K / (16 * NW);
+    if (steps >= 8) return go(head_tile_kernel<ACT, POOLED, NW, 8>);
+    if (steps >= 4) return go(head_tile_kernel<ACT, POOLED, NW, 4>);
+    if (steps >= 2) return go(head_tile_kernel<ACT, POOLED, NW, 2>);
+    return go(head_tile_kernel<ACT, POOLED, NW, 1>);
+}
+
 template <int ACT, bool POOLED>
 hipError_t fc(const float* in, const float* hidden, const float* z, const int32_t* start, int pooling, int n, int K,
               int N, const float* w, const float* b, float* out, hipStream_t st) {
-    if (N % 16 == 0 && K % 128 == 0) {
-        ELIS_TRY(launch_kernel((head_tile_kernel<ACT, POOLED, 8>), dim3(N / 16, (n + 15) / 16), dim3(8 * kWave), 0, st,
-                               in, hidden, z, start, pooling, n, K, N, w, b, out));
-    } else if (N % 16 == 0 && K % 64 == 0) {
-        ELIS_TRY(launch_kernel((head_tile_kernel<ACT, POOLED, 4>), dim3(N / 16, (n + 15) / 16), dim3(4 * kWave), 0, st,
-                               in, hidden, z, start, pooling, n, K, N, w, b, out));
-    } else {
-        ELIS_TRY(launch_kernel((head_fc_kernel<ACT, POOLED>), dim3(N, (n + kFcSeq - 1) / kFcSeq), dim3(kWave), 0, st,
-                               in, hidden, z, start, pooling, n, K, N, w, b, out));
-    }
-    return hipSuccess;
+    if (N % 16 == 0 && K % 128 == 0) return fc_tile<ACT, POOLED, 8>(in, hidden, z, start, pooling, n, K, N, w, b, out, st);
+    if (N % 16 == 0 && K % 64 == 0) return fc_tile<ACT, POOLED, 4>(in, hidden, z, start, pooling, n, K, N, w, b, out, st);
+    return launch_kernel((head_fc_kernel<ACT, POOLED>), dim3(N, (n + kFcSeq - 1) / kFcSeq), dim3(kWave), 0, st, in, hidden, z,
+                         start, pooling, n, K, N, w, b, out);
 }
 
 hipError_t launch_fc(int act, bool pooled, const float* in, const float* hidden, const float* z,
