@@ -33,6 +33,8 @@ namespace elis {
 
 namespace {
 
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;  // four floats at any float's address
+
 constexpr int kCols = 256;      // columns per pooling work-group
 constexpr int kFcSeq = 8;  // sequences sharing one weight-row read in head_fc
 
@@ -147,8 +149,9 @@ __global__ __launch_bounds__(kWave) void head_fc_kernel(const float* __restrict_
 // summed through LDS in wave order, the bias added and the activation applied by wave 0.
 // Every output depends on its own sequence's row only, in a fixed order: results do not depend
 // on how many sequences are batched. grid (N / 16, ceil(n / 16)), NW waves; K % (16 NW) == 0.
-// BATCH: steps of 16 inputs in LDS at once, 2 NW KB of LDS each.
-template <int ACT, bool POOLED, int NW, int BATCH>
+// BATCH: steps of 16 inputs in LDS at once, 2 NW KB of LDS each. DIRECT: rows are 16-byte aligned and loaded
+// straight into LDS; else they go through registers, which takes any float's alignment.
+template <int ACT, bool POOLED, int NW, int BATCH, bool DIRECT>
 __global__ __launch_bounds__(NW* kWave) void head_tile_kernel(const float* __restrict__ in,
                                                               const float* __restrict__ hidden,
                                                               const float* __restrict__ z,
@@ -177,8 +180,13 @@ __global__ __launch_bounds__(NW* kWave) void head_tile_kernel(const float* __res
         constexpr int COUNT = decltype(count_c)::value;
 #pragma unroll
         for (int u = 0; u < COUNT; ++u) {
-            gemm::load_lds_16(xl + 16 * (m0 + u), stage[wv][u][0]);
-            gemm::load_lds_16(wl + 16 * (m0 + u), stage[wv][u][1]);
+            if constexpr (DIRECT) {
+                gemm::load_lds_16(xl + 16 * (m0 + u), stage[wv][u][0]);
+                gemm::load_lds_16(wl + 16 * (m0 + u), stage[wv][u][1]);
+            } else {
+                *reinterpret_cast<f32x4*>(&stage[wv][u][0][4 * lane]) = *reinterpret_cast<const f32x4_any*>(xl + 16 * (m0 + u));
+                *reinterpret_cast<f32x4*>(&stage[wv][u][1][4 * lane]) = *reinterpret_cast<const f32x4_any*>(wl + 16 * (m0 + u));
+            }
         }
         // Step by step as the loads land, each read ahead of the block before it.
         f32x4 xv[COUNT], wq[COUNT];
@@ -264,10 +272,12 @@ hipError_t fc_tile(const float* in, const float* hidden, const float* z, const i
     };
     // LDS for the steps a wave has, no more: with room for eight of them a CU holds one work-group whatever the depth.
     const int steps = K / (16 * NW);
-    if (steps >= 8) return go(head_tile_kernel<ACT, POOLED, NW, 8>);
-    if (steps >= 4) return go(head_tile_kernel<ACT, POOLED, NW, 4>);
-    if (steps >= 2) return go(head_tile_kernel<ACT, POOLED, NW, 2>);
-    return go(head_tile_kernel<ACT, POOLED, NW, 1>);
+    const uintptr_t rows = reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(POOLED && pooling == ELIS_POOL_CLS ? hidden : POOLED ? z : in);
+    if (rows & 15u) return go(head_tile_kernel<ACT, POOLED, NW, 1, false>);
+    if (steps >= 8) return go(head_tile_kernel<ACT, POOLED, NW, 8, true>);
+    if (steps >= 4) return go(head_tile_kernel<ACT, POOLED, NW, 4, true>);
+    if (steps >= 2) return go(head_tile_kernel<ACT, POOLED, NW, 2, true>);
+    return go(head_tile_kernel<ACT, POOLED, NW, 1, true>);
 }
 
 template <int ACT, bool POOLED>
