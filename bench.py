@@ -117,6 +117,8 @@ _GEMM_EPI = {"gemm_qkv": (0, 0), "gemm_o": (2, 4), "gemm_ffn1": (1, 1), "gemm_ff
 def _gemm_kernel(bm, bn, wgs, epi, n, f32):
     if (bm, bn) == (256, 256):
         return f"gemm_persist_kernel<{epi}>"
+    if (bm, bn) == (32, 32):
+        return f"gemm_wave_kernel<{epi}>"
     if (bm, bn) == (128, 128):
         return f"gemm_sched_kernel<128, 128, 2, 2, 32, {epi}, 2, 2>"
     if (bm, bn) == (64, 128):
@@ -129,9 +131,8 @@ def _gemm_kernel(bm, bn, wgs, epi, n, f32):
 def class_kernels(workload: str) -> dict:
     """class -> (kernel names any launch of the class dispatches, sources, launches per pass).
     A GEMM class uses the plan at T rows (one or two kernels) and, with CLS pooling, the plan at
-    n rows in the last layer, or 32 x 32 tiles in its place where the library prices them lower (up to
-    512 tiles); the out-projection of that layer also gathers its residual rows. Attention has a narrow
-    form for small launches. A summary counts the names that its run dispatched (_dispatched)."""
+    n rows in the last layer; the out-projection of that layer also gathers its residual rows. Attention has
+    a narrow form for small launches. A summary counts the names that its run dispatched (_dispatched)."""
     from paper_2505_09142_amd import _elis as E
     from workloads import WORKLOADS, make_batch
     w = WORKLOADS[workload]
@@ -152,15 +153,14 @@ def class_kernels(workload: str) -> dict:
                     [_gemm_kernel(rbm, rbn, rwg, internal, nn, pub == 2)] if m1 < m else []):
                 if kname not in names:
                     names.append(kname)
-            few = f"gemm_wave_kernel<{internal}>"
-            if nn % 128 == 0 and (m + 31) // 32 * (nn // 32) <= 512 and few not in names:
-                names.append(few)
         if cls == "gemm_o" and cls_tail:
             names.append("gather_rows_kernel")
         out[cls] = (names, _GEMM_SRC, L)
     vpl = (d + 255) // 256
-    att = [f"attention_kernel<{d // s.n_heads}, false>", f"attention_narrow_kernel<{d // s.n_heads}>"] + ([f"attention_kernel<{d // s.n_heads}, true>"] if cls_tail
-                                                             else [])
+    dh = d // s.n_heads
+    att = [f"attention_kernel<{dh}, false>", f"attention_narrow_kernel<{dh}>"]
+    if cls_tail:
+        att.append(f"attention_kernel<{dh}, true>")
     out["attention"] = (att, ["paper_2505_09142_amd/csrc/attention.hip", "paper_2505_09142_amd/csrc/common.h"], L)
     out["layernorm"] = ([f"layernorm_kernel<{vpl}>"], ["paper_2505_09142_amd/csrc/norm.hip",
                                                         "paper_2505_09142_amd/csrc/common.h"], 2 * L)
@@ -582,7 +582,7 @@ def select_sweep(ks=(64, 8192), iters=20):
 GEMM_PLAN_SHAPES = (  # (name, N, K, public epilogue): the encoder products of BERT-base and XLM-R-large
     ("bert_qkv", 2304, 768, 0), ("bert_ffn1", 3072, 768, 1), ("bert_o", 768, 768, 2), ("bert_ffn2", 768, 3072, 2),
     ("xlmr_qkv", 3072, 1024, 0), ("xlmr_ffn1", 4096, 1024, 1), ("xlmr_o", 1024, 1024, 2), ("xlmr_ffn2", 1024, 4096, 2))
-GEMM_PLAN_MS = (1024, 2560, 4096, 6144, 8192, 10240, 12288, 14336, 16384, 18432, 20480, 22528, 23931, 26624, 28672,
+GEMM_PLAN_MS = (64, 193, 512, 1024, 2560, 4096, 6144, 8192, 10240, 12288, 14336, 16384, 18432, 20480, 22528, 23931, 26624, 28672,
                 30720, 32768, 47000, 92000)
 GEMM_PLAN_PROFILE = os.path.join(ROOT, "profiles", "gemm_launch_plans.md")
 
@@ -611,7 +611,7 @@ def gemm_plans(reps=8):
         tiles = [t for t in ((256, 256, 1), (128, 128, 2), (64, 128, 2), (64, 128, 1), (64, 64, 4), (64, 64, 2))
                  if n % t[1] == 0]
         for m in GEMM_PLAN_MS:
-            plans = []
+            plans = [(32, 32, 2, m, 0, 0, 0)] if -(-m // 32) * (n // 32) <= 512 else []
             for t in tiles:
                 plans.append(t + (m, 0, 0, 0))
                 per_row, slots = n // t[1], t[2] * cus
@@ -767,7 +767,7 @@ def summarize_gemm_plans(js, command):
              "For each encoder product of BERT-base and XLM-R-large (fp32-out products with the plain residual) "
              "and each token count M, every plan the library can choose from is timed through "
              "`elis_linear_with_plan`: one launch of tiles (written rows×columns/work-groups per CU: 256×256/1, "
-             "128×128/2, 64×128/2, 64×128/1 with 4 stages, 64×64/4, 64×64/2 with 4 stages), or large tiles over "
+             "128×128/2, 64×128/2, 64×128/1 with 4 stages, 64×64/4, 64×64/2 with 4 stages, and 32×32/2 up to 512 of them), or large tiles over "
              "the rows that fill whole rounds plus a second launch of another "
              "configuration over the rest. `chosen` is `elis_linear_plan`'s pick (the launch-time model); "
              "`fastest` the best measured; the fixed columns are what one configuration alone takes.", "",

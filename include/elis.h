@@ -318,9 +318,7 @@ int elis_linear(const uint16_t *x, const uint16_t *w, const float *bias, const f
  * the three rest fields are 0). The plan comes from a launch-time model of the
  * tile configurations and the device's compute-unit count; every plan gives
  * bit-identical results (except that the 128 x 64 tile, used only when n is
- * an odd multiple of 64, accumulates with 16 x 16 x 32 blocks). Few rows (at
- * most 512 tiles of 32 x 32) run in one launch of such tiles instead where the
- * model prices it below the plan, with the same bits. Errors: as
+ * an odd multiple of 64, accumulates with 16 x 16 x 32 blocks). Errors: as
  * elis_linear (ELIS_EINVAL, ELIS_EUNSUPPORTED), and ELIS_EINVAL on a null out.
  */
 int elis_linear_plan(int32_t m, int32_t n, int32_t k, int32_t epilogue, int32_t *out);
@@ -329,9 +327,10 @@ int elis_linear_plan(int32_t m, int32_t n, int32_t k, int32_t epilogue, int32_t 
  * elis_linear with the launch plan given instead of chosen: plan[7] in the
  * layout elis_linear_plan writes. Tiles: 256 x 256 (1 work-group per CU),
  * 128 x 128 (2), 64 x 128 (2 or 1; the latter four-stage), 64 x 64 (4 or 2;
- * the latter four-stage), 128 x 64 (2;
- * single launch, and only for n an odd multiple of 64, where it is the only
- * tile); main_bn and rest_bn must divide n, 1 <= m1 <= m, m1 a multiple of
+ * the latter four-stage), 32 x 32 (2; single launch, n a multiple of 128 up to
+ * 2^20, k up to 2^21), 128 x 64 (2; single launch, and only for n an odd
+ * multiple of 64, where it is the only tile). 256 x 256 stands for 128 x 128
+ * tiles where k = 64, k > 2^21 or n > 2^20, and is not chosen there. main_bn and rest_bn must divide n, 1 <= m1 <= m, m1 a multiple of
  * main_bm when m1 < m, rest different from main. Every valid plan gives the
  * same bits as elis_linear; meant for benchmarking and re-fitting the launch
  * model on other hardware. Errors: as elis_linear, and ELIS_EINVAL for a null

@@ -223,18 +223,14 @@ int check_linear(const uint16_t* x, const uint16_t* w, const float* bias, const 
     return ELIS_OK;
 }
 
-// plan: null where the library chooses the launch.
-int run_linear(const GemmPlan* plan, const uint16_t* x, const uint16_t* w, const float* bias, const float* residual,
+int run_linear(const GemmPlan& p, const uint16_t* x, const uint16_t* w, const float* bias, const float* residual,
                int32_t m, int32_t n, int32_t k, int32_t epilogue, void* out, void* stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int cls = epilogue == ELIS_EPI_BIAS_GELU_BF16 ? ELIS_K_GEMM_FFN1
                     : epilogue == ELIS_EPI_BIAS_RES_F32 ? ELIS_K_GEMM_FFN2
                                                         : ELIS_K_GEMM_QKV;
     const Residual res{epilogue == ELIS_EPI_BIAS_RES_F32 ? residual : nullptr, nullptr, nullptr, nullptr};
-    return status_of(timed(cls, [&] {
-        return plan ? launch_gemm_plan(*plan, x, w, bias, res, m, n, k, epilogue, out, st)
-                    : launch_gemm(x, w, bias, res, m, n, k, epilogue, out, st);
-    }));
+    return status_of(timed(cls, [&] { return launch_gemm_plan(p, x, w, bias, res, m, n, k, epilogue, out, st); }));
 }
 
 }  // namespace
@@ -619,7 +615,7 @@ int elis_linear(const uint16_t* x, const uint16_t* w, const float* bias, const f
                 int32_t k, int32_t epilogue, void* out, void* stream) {
     const int v = check_linear(x, w, bias, residual, m, n, k, epilogue, out);
     if (v != ELIS_OK) return v;
-    return run_linear(nullptr, x, w, bias, residual, m, n, k, epilogue, out, stream);
+    return run_linear(plan_gemm(m, n, k, epilogue), x, w, bias, residual, m, n, k, epilogue, out, stream);
 }
 
 int elis_linear_with_plan(const uint16_t* x, const uint16_t* w, const float* bias, const float* residual, int32_t m,
@@ -630,16 +626,17 @@ int elis_linear_with_plan(const uint16_t* x, const uint16_t* w, const float* bia
     GemmPlan p{gemm_config_of_tile(plan[0], plan[1], plan[2]), plan[3], 0};
     if (p.main < 0 || n % plan[1] != 0 || p.m1 < 1 || p.m1 > m) return ELIS_EINVAL;
     if (p.main == 1 && n % 128 == 0) return ELIS_EINVAL;  // 128 x 64 only where nothing else fits
+    if (p.main == kWaveCfg && (p.m1 < m || !gemm_wave_fits(n, k))) return ELIS_EINVAL;
     if (p.m1 < m) {
         p.rest = gemm_config_of_tile(plan[4], plan[5], plan[6]);
         // the 16 x 16 x 32 configuration accumulates in another order: single launches only
-        if (p.rest < 0 || p.rest == p.main || p.main == 1 || p.rest == 1 || n % plan[5] != 0 ||
+        if (p.rest < 0 || p.rest == p.main || p.rest == kWaveCfg || p.main == 1 || p.rest == 1 || n % plan[5] != 0 ||
             p.m1 % plan[0] != 0)
             return ELIS_EINVAL;
     } else if (plan[4] || plan[5] || plan[6]) {
         return ELIS_EINVAL;
     }
-    return run_linear(&p, x, w, bias, residual, m, n, k, epilogue, out, stream);
+    return run_linear(p, x, w, bias, residual, m, n, k, epilogue, out, stream);
 }
 
 size_t elis_attention_workspace_bytes(int32_t n_seqs, int32_t total_tokens) {

@@ -7,8 +7,7 @@
 // row statistics (Residual in kernels.h).
 //
 // Four kernels; launch_gemm plans each product (plan_gemm: one launch, or a
-// launch of large tiles over whole rounds plus one of small tiles over the remaining rows;
-// gemm_few_rows: 32 x 32 tiles instead):
+// launch of large tiles over whole rounds plus one of small tiles over the remaining rows):
 //   gemm_kernel        register-staged k-slabs, 16 x 16 x 32 MFMA blocks; for N that
 //                      is an odd multiple of 64;
 //   gemm_sched_kernel  k-slabs go HBM -> LDS with global_load_lds_dwordx4 (no register
@@ -990,24 +989,15 @@ hipError_t launch_wave(const uint16_t* x, const uint16_t* w, const float* bias, 
 template <int BM, int BN, int WM, int WN, int MI, int OCC = 1, int S = 2>
 hipError_t launch_sched(const uint16_t* x, const uint16_t* w, const float* bias, Residual res, int m, int n,
                         int k, int epi, void* out, hipStream_t st, int group_m) {
-    if constexpr (BM == 256 && BN == 256) {
-        // The persistent kernel needs two k-slabs and 32-bit offsets inside a tile's operands and output; other
-        // products of this configuration take 128 x 128 tiles (the same bits; at k = 64 also the faster tile:
-        // 3.8 against 5.6 us at 300 x 256).
-        if (k >= 2 * kBK && k <= (1 << 21) && n <= (1 << 20))
-            return launch_persist(x, w, bias, res, m, n, k, epi, out, st, group_m);
-        return launch_sched<128, 128, 2, 2, 32, 2>(x, w, bias, res, m, n, k, epi, out, st, group_m);
-    } else {
-        const dim3 grid(((m + BM - 1) / BM) * (n / BN)), block(WM * WN * kWave);
-        auto go = [&](auto kernel) { return launch_kernel(kernel, grid, block, 0, st, x, w, bias, res, out, m, n, k, group_m); };
-        switch (epi) {
-            case ELIS_EPI_BIAS_BF16: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, ELIS_EPI_BIAS_BF16, OCC, S>);
-            case ELIS_EPI_BIAS_GELU_BF16: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, ELIS_EPI_BIAS_GELU_BF16, OCC, S>);
-            case ELIS_EPI_BIAS_RES_F32: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, ELIS_EPI_BIAS_RES_F32, OCC, S>);
-            case kEpiResLn: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, kEpiResLn, OCC, S>);
-            case kEpiResLnFfn2: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, kEpiResLnFfn2, OCC, S>);
-            default: return hipErrorInvalidValue;
-        }
+    const dim3 grid(((m + BM - 1) / BM) * (n / BN)), block(WM * WN * kWave);
+    auto go = [&](auto kernel) { return launch_kernel(kernel, grid, block, 0, st, x, w, bias, res, out, m, n, k, group_m); };
+    switch (epi) {
+        case ELIS_EPI_BIAS_BF16: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, ELIS_EPI_BIAS_BF16, OCC, S>);
+        case ELIS_EPI_BIAS_GELU_BF16: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, ELIS_EPI_BIAS_GELU_BF16, OCC, S>);
+        case ELIS_EPI_BIAS_RES_F32: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, ELIS_EPI_BIAS_RES_F32, OCC, S>);
+        case kEpiResLn: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, kEpiResLn, OCC, S>);
+        case kEpiResLnFfn2: return go(gemm_sched_kernel<BM, BN, WM, WN, MI, kEpiResLnFfn2, OCC, S>);
+        default: return hipErrorInvalidValue;
     }
 }
 
@@ -1044,17 +1034,26 @@ hipError_t launch_tile(const uint16_t* x, const uint16_t* w, const float* bias, 
 
 }  // namespace
 
+// The persistent kernel needs two k-slabs, and both it and the 32 x 32 tiles 32-bit offsets inside a tile's operands
+// and output. The 32 x 32 tiles leave an n that is an odd multiple of 64 to the kernel that accumulates it in
+// 16 x 16 x 32 blocks.
+bool gemm_persist_fits(int n, int k) { return n % 256 == 0 && k >= 2 * kBK && k <= (1 << 21) && n <= (1 << 20); }
+bool gemm_wave_fits(int n, int k) { return n % 128 == 0 && k <= (1 << 21) && n <= (1 << 20); }
+
 // Tile configurations (ids are internal; benchmarks sweep them).
 hipError_t launch_gemm_config(int cfg, int group_m, const uint16_t* x, const uint16_t* w, const float* bias,
                               Residual res, int m, int n, int k, int epi, void* out, hipStream_t st) {
     switch (cfg) {
         case 1: return launch_tile<128, 64, 2, 2, 16>(x, w, bias, res, m, n, k, epi, out, st);
-        case 21: return launch_sched<256, 256, 2, 4, 32>(x, w, bias, res, m, n, k, epi, out, st, group_m);
+        case kPersistCfg:  // other depths: the same bits in 128 x 128 tiles
+            if (gemm_persist_fits(n, k)) return launch_persist(x, w, bias, res, m, n, k, epi, out, st, group_m);
+            return launch_sched<128, 128, 2, 2, 32, 2>(x, w, bias, res, m, n, k, epi, out, st, group_m);
         case 32: return launch_sched<128, 128, 2, 2, 32, 2>(x, w, bias, res, m, n, k, epi, out, st, group_m);
         case 33: return launch_sched<64, 128, 2, 2, 32, 2>(x, w, bias, res, m, n, k, epi, out, st, group_m);
         case 34: return launch_sched<64, 128, 2, 2, 32, 1, 4>(x, w, bias, res, m, n, k, epi, out, st, group_m);
         case 35: return launch_sched<64, 64, 2, 2, 32, 4, 2>(x, w, bias, res, m, n, k, epi, out, st, group_m);
         case 36: return launch_sched<64, 64, 2, 2, 32, 2, 4>(x, w, bias, res, m, n, k, epi, out, st, group_m);
+        case kWaveCfg: return gemm_wave_fits(n, k) ? launch_wave(x, w, bias, res, m, n, k, epi, out, st) : hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
 }
@@ -1063,8 +1062,8 @@ namespace {
 struct TileShape {
     int cfg, bm, bn, wgs_per_cu;
 };
-constexpr TileShape kTileShapes[] = {{1, 128, 64, 2},   {21, 256, 256, 1}, {32, 128, 128, 2}, {33, 64, 128, 2},
-                                     {34, 64, 128, 1},  {35, 64, 64, 4},   {36, 64, 64, 2}};
+constexpr TileShape kTileShapes[] = {{1, 128, 64, 2},  {21, 256, 256, 1}, {32, 128, 128, 2}, {33, 64, 128, 2},
+                                     {34, 64, 128, 1}, {35, 64, 64, 4},   {36, 64, 64, 2},   {40, 32, 32, 2}};
 }  // namespace
 
 void gemm_config_tile(int cfg, int* bm, int* bn, int* wgs_per_cu) {
@@ -1116,7 +1115,7 @@ constexpr TileModel kTileModels[] = {
      {{2.83f, 2.93f, 3.18f, 1.29f}, {3.29f, 3.07f, 3.61f, 1.50f}, {3.35f, 3.86f, 4.78f, 2.16f}}},
 };
 // The one-wave 32 x 32 tile, up to one round and never beside another launch (beta unused).
-constexpr TileModel kWaveModel = {0, 32, 32, 2, 1, {0.125f, 0.126f, 0.176f, 0.f},
+constexpr TileModel kWaveModel = {kWaveCfg, 32, 32, 2, 1, {0.125f, 0.126f, 0.176f, 0.f},
                                   {{2.62f, 2.83f, 2.66f, 0.f}, {2.88f, 3.09f, 2.94f, 0.f}, {2.68f, 2.82f, 3.04f, 0.f}}};
 constexpr float kSecondLaunchUs = 1.0f;  // dispatch cost of the remainder launch
 
@@ -1150,15 +1149,15 @@ double model_us(const TileModel& t, int kind, long long m, int n, int k, long lo
 // as two rounds of the 128 x 128 pairs, but a round that is only partly filled costs nearly a
 // full one, so the rows past the last full round of large tiles go to a configuration whose
 // tiles are small enough to finish them in one short round.
-GemmPlan plan_gemm(int m, int n, int k, int epi, double* us) {
-    if (us) *us = 0.0;
+GemmPlan plan_gemm(int m, int n, int k, int epi) {
     if (n % 128 != 0) return {1, m, 0};
     const int kind = epilogue_kind(epi);
     const long long cus = device_cus();
-    GemmPlan best{21, m, 0};
+    GemmPlan best{0, m, 0};
     double best_us = -1.0;
+    auto fits = [&](const TileModel& t) { return n % t.bn == 0 && (t.cfg != kPersistCfg || gemm_persist_fits(n, k)); };
     for (const TileModel& main : kTileModels) {
-        if (n % main.bn != 0) continue;
+        if (!fits(main)) continue;
         const double t = model_us(main, kind, m, n, k, cus);
         if (best_us < 0.0 || t < best_us) {
             best_us = t;
@@ -1171,7 +1170,7 @@ GemmPlan plan_gemm(int m, int n, int k, int epi, double* us) {
         if (m1 <= 0 || m1 >= m) continue;
         const double head = model_us(main, kind, m1, n, k, cus) + kSecondLaunchUs;
         for (const TileModel& rest : kTileModels) {
-            if (rest.cfg == main.cfg || n % rest.bn != 0) continue;
+            if (rest.cfg == main.cfg || !fits(rest)) continue;
             const double tr = head + model_us(rest, kind, m - m1, n, k, cus);
             if (tr < best_us) {
                 best_us = tr;
@@ -1179,16 +1178,10 @@ GemmPlan plan_gemm(int m, int n, int k, int epi, double* us) {
             }
         }
     }
-    if (us) *us = best_us;
+    // 32 x 32 tiles where they fill at most one round (512 tiles) and the model prices them lower: up to about 540 rows
+    // at n = 768 or 1,024, 200 at n = 2,304 and 150 at n = 3,072 or 4,096.
+    if (gemm_wave_fits(n, k) && model_us(kWaveModel, kind, m, n, k, cus) < best_us) best = {kWaveCfg, m, 0};
     return best;
-}
-
-// Whether the product runs in 32 x 32 tiles: where those fill at most one round (512 tiles) and the model prices
-// them below the plan. That is up to about 540 rows at n = 768 or 1,024, 200 at n = 2,304 and 150 at n = 3,072
-// or 4,096.
-bool gemm_few_rows(int m, int n, int k, int epi, double plan_us) {
-    if (n % 128 != 0 || k > (1 << 21) || n > (1 << 20)) return false;  // 32-bit offsets inside a tile's operands
-    return model_us(kWaveModel, epilogue_kind(epi), m, n, k, device_cus()) < plan_us;
 }
 
 hipError_t launch_gemm_plan(const GemmPlan& p, const uint16_t* x, const uint16_t* w, const float* bias,
@@ -1212,10 +1205,7 @@ hipError_t launch_gemm_plan(const GemmPlan& p, const uint16_t* x, const uint16_t
 hipError_t launch_gemm(const uint16_t* x, const uint16_t* w, const float* bias, Residual res, int m, int n,
                        int k, int epi, void* out, hipStream_t st) {
     if (m < 1 || n % 64 != 0 || k % kBK != 0 || n < 64 || k < kBK) return hipErrorInvalidValue;
-    double us = 0.0;
-    const GemmPlan p = plan_gemm(m, n, k, epi, &us);
-    if (gemm_few_rows(m, n, k, epi, us)) return launch_wave(x, w, bias, res, m, n, k, epi, out, st);
-    return launch_gemm_plan(p, x, w, bias, res, m, n, k, epi, out, st);
+    return launch_gemm_plan(plan_gemm(m, n, k, epi), x, w, bias, res, m, n, k, epi, out, st);
 }
 
 }  // namespace elis

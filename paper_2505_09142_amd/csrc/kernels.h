@@ -53,13 +53,16 @@ constexpr int kEpiResLnFfn2 = 5;
 hipError_t launch_gemm(const uint16_t* x, const uint16_t* w, const float* bias, Residual res, int m, int n,
                        int k, int epi, void* out, hipStream_t st);
 
-// Tile plan of one product (gemm.hip; launch_gemm may run few rows in 32 x 32 tiles instead): rows [0, m1) with configuration `main`, then, when
+// Launch plan of one product (gemm.hip): rows [0, m1) with configuration `main`, then, when
 // m1 < M, rows [m1, M) with configuration `rest`.
 struct GemmPlan {
     int main, m1, rest;
 };
-// us: the model's time for it (0 where it prices none), or null.
-GemmPlan plan_gemm(int m, int n, int k, int epi, double* us = nullptr);
+GemmPlan plan_gemm(int m, int n, int k, int epi);
+constexpr int kPersistCfg = 21;  // 256 x 256 tiles
+constexpr int kWaveCfg = 40;     // 32 x 32 tiles, one launch only
+bool gemm_persist_fits(int n, int k);
+bool gemm_wave_fits(int n, int k);
 hipError_t launch_gemm_plan(const GemmPlan& p, const uint16_t* x, const uint16_t* w, const float* bias,
                             Residual res, int m, int n, int k, int epi, void* out, hipStream_t st);
 // Tile of a configuration (zeros if unknown) and the configuration of a tile (-1 if none).

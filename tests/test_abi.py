@@ -187,7 +187,7 @@ def test_linear_plan_host_only(lib):
     """The launch plan of a product is host arithmetic: rows split at a whole number of main-tile
     rows, the two launches cover [0, m), tiles of the shapes the library has, and the arguments
     elis_linear rejects are rejected here too."""
-    tiles = {(64, 64), (64, 128), (128, 64), (128, 128), (256, 256)}
+    tiles = {(32, 32), (64, 64), (64, 128), (128, 64), (128, 128), (256, 256)}
     rng = np.random.default_rng(5)
     splits = 0
     for _ in range(400):
@@ -212,6 +212,8 @@ def test_linear_plan_host_only(lib):
             assert (rbm, rbn, rwg) == (0, 0, 0)
     assert splits > 20
     assert E.elis_linear_plan(23931, 768, 3072, E.ELIS_EPI_BIAS_RES_F32)[1][3] < 23931
+    assert E.elis_linear_plan(193, 768, 3072, E.ELIS_EPI_BIAS_RES_F32)[1] == (32, 32, 2, 193, 0, 0, 0)
+    assert E.elis_linear_plan(30000, 512, 64, 0)[1][:2] != (256, 256)  # needs two k-slabs
     assert E.elis_linear_plan(0, 768, 768, 0)[0] == E.ELIS_EINVAL
     assert E.elis_linear_plan(100, 100, 768, 0)[0] == E.ELIS_EUNSUPPORTED
     assert E.elis_linear_plan(100, 768, 100, 0)[0] == E.ELIS_EUNSUPPORTED
@@ -234,6 +236,9 @@ def test_linear_with_plan_rejects_invalid_plans(lib):
     assert call((128, 128, 2, 512, 0, 0, 0)) == E.ELIS_EINVAL        # rest missing
     assert call((128, 64, 2, 1000, 0, 0, 0)) == E.ELIS_EINVAL        # 128 x 64 only for n = 64 mod 128
     assert call((256, 256, 1, 512, 128, 64, 2), n=768) == E.ELIS_EINVAL
+    assert call((32, 32, 2, 512, 64, 64, 2)) == E.ELIS_EINVAL        # 32 x 32 only alone
+    assert call((128, 128, 2, 512, 32, 32, 2)) == E.ELIS_EINVAL
+    assert call((32, 32, 2, 1000, 0, 0, 0), n=192) == E.ELIS_EINVAL  # and where n is a multiple of 128
     assert call((128, 128, 2, 1000, 0, 0, 0), n=100) == E.ELIS_EUNSUPPORTED
 
 

@@ -19,7 +19,11 @@ at the sizes the plan sweep times. The checks:
 * the epilogue's LDS staging (writes and read-back) stays inside the stage
   buffers and inside the wave's own rows;
 * a two-launch plan's second launch (row offset m1) addresses only rows
-  [m1, M) of the full buffers.
+  [m1, M) of the full buffers;
+* the kernels that load through buffer resources (the persistent 256 x 256 kernel and the 32 x 32
+  one-wave kernel) form resources that lie inside their buffers, and exactly the rows past the end
+  of the matrix fall outside them; their load streams ask for every slab once, in the order in
+  which it is multiplied, and never load over a slab that is still to be read.
 
 The configuration list is read from gemm.hip itself (the launch_gemm_config
 switch and kTileShapes), so a configuration added there without a mirror here
@@ -39,15 +43,17 @@ WAVE = 64
 BK = 64
 GROUP_M = 8
 
-# id -> (kind, BM, BN, WM, WN, MI, OCC, S); kind "sched" = gemm_sched_kernel, "reg" = gemm_kernel
+# id -> (kind, BM, BN, WM, WN, MI, OCC, S); kind "sched" = gemm_sched_kernel, "reg" = gemm_kernel,
+# "persist" = gemm_persist_kernel (128 x 128 tiles of gemm_sched_kernel where k = 64), "wave" = gemm_wave_kernel
 CONFIGS = {
     1: ("reg", 128, 64, 2, 2, 16, 2, 2),
-    21: ("sched", 256, 256, 2, 4, 32, 1, 2),
+    21: ("persist", 256, 256, 2, 4, 32, 1, 2),
     32: ("sched", 128, 128, 2, 2, 32, 2, 2),
     33: ("sched", 64, 128, 2, 2, 32, 2, 2),
     34: ("sched", 64, 128, 2, 2, 32, 1, 4),
     35: ("sched", 64, 64, 2, 2, 32, 4, 2),
     36: ("sched", 64, 64, 2, 2, 32, 2, 4),
+    40: ("wave", 32, 32, 1, 1, 32, 2, 8),
 }
 EPIS = (E.ELIS_EPI_BIAS_BF16, E.ELIS_EPI_BIAS_GELU_BF16, E.ELIS_EPI_BIAS_RES_F32)
 TILE_TO_CFG = {(v[1], v[2], v[6]): c for c, v in CONFIGS.items()}  # (bm, bn, work-groups per CU) -> id
@@ -55,7 +61,16 @@ TILE_TO_CFG = {(v[1], v[2], v[6]): c for c, v in CONFIGS.items()}  # (bm, bn, wo
 
 def test_mirror_covers_every_configuration():
     src = open(GEMM_SRC).read()
+    ids = dict(re.findall(r"constexpr int (kPersistCfg|kWaveCfg) = (\d+);", open(os.path.join(os.path.dirname(GEMM_SRC), "kernels.h")).read()))
     found = {}
+    for name, kind in (("kPersistCfg", "persist"), ("kWaveCfg", "wave")):
+        cases = re.search(rf"case {name}:(.*?)(?=case |default)", src, re.S).group(1)
+        assert f"launch_{kind}(" in cases and f"gemm_{kind}_fits(n, k)" in cases
+        found[int(ids[name])] = CONFIGS[int(ids[name])]
+        if kind == "persist":
+            assert "return launch_sched<128, 128, 2, 2, 32, 2>(" in cases
+    assert "constexpr int BM = 256, BN = 256, HALF = 128 * kBK, STAGE = 4 * HALF, STG = 2048;" in src
+    assert "constexpr int RING = 8, SLAB = 64 * kBK;" in src
     for cid, kind, args in re.findall(r"case (\d+): return launch_(sched|tile)<([^>]*)>", src):
         v = [int(x) for x in args.split(",")]
         bm, bn, wm, wn, mi = v[:5]
@@ -304,10 +319,207 @@ def check_reg(M, N, K, epi, cfg, full_cover):
         assert np.all(written == 1)
 
 
+# ----------------------------------------------------------------------------- persistent kernel
+
+CUS = 256
+
+
+def persist_tiles(bid, grid, tiles):
+    """Tiles of one work-group: its XCD's contiguous range, dealt out to the XCD's work-groups."""
+    xcd, per, rem = bid & 7, tiles >> 3, tiles & 7
+    count = per + (xcd < rem)
+    end = xcd * per + min(xcd, rem) + count
+    return list(range(end - count + (bid >> 3), end, (grid - xcd + 7) >> 3)), end
+
+
+def check_persist_stream(tiles, t_end, K):
+    """Slabs are requested two ahead of the one that is multiplied, across tiles, then as empty loads."""
+    wgs = tiles[1] - tiles[0] if len(tiles) > 1 else 1 << 30
+    lt, lk, more, asked = tiles[0], 0, True, []
+
+    def request():
+        nonlocal lt, lk, more
+        asked.append((lt, lk // (2 * BK)) if more else None)
+        assert lk + 2 * BK <= 2 * K  # inside a row of k elements; 0 for an empty resource
+        lk += 2 * BK if more else 0
+        if lk == 2 * K:
+            lk, lt = 0, lt + wgs
+            more = lt < t_end
+
+    request()
+    request()
+    for _ in range(len(tiles) * (K // BK)):
+        request()
+    want = [(t, k) for t in tiles for k in range(K // BK)]
+    assert asked[:len(want)] == want and all(a is None for a in asked[len(want):])
+
+
+def check_persist(M, N, K, epi, cfg, full_cover):
+    """gemm_persist_kernel<EPI>: byte offsets within buffer resources of a tile's own rows."""
+    assert K >= 2 * BK
+    BM = BN = 256
+    STAGE_B, STG_B = 4 * 128 * BK * 2, 4096  # bytes of a stage and of a wave's staging area
+    assert 2 * STAGE_B + 8 * STG_B <= 160 * 1024
+    tiles_m, tiles_n = -(-M // BM), N // BN
+    tiles, grid = tiles_m * tiles_n, min(tiles_m * tiles_n, CUS)
+    walked = [persist_tiles(b, grid, tiles) for b in range(grid)]
+    assert sorted(sum((w for w, _ in walked), [])) == list(range(tiles)) and all(w for w, _ in walked)
+    for b in sorted({0, grid - 1}):
+        check_persist_stream(*walked[b], K)
+    tm, tn = grouped_tile(np.arange(tiles), tiles_m, tiles_n, GROUP_M)
+    assert np.array_equal(np.sort(tm * tiles_n + tn), np.arange(tiles))
+    tm, tn = corner_tiles(tm, tn, tiles_m, tiles_n, full_cover)
+    wid, lane = np.arange(8)[:, None], np.arange(WAVE)[None, :]
+    wm, wn = wid >> 2, wid & 3
+    rl, kg = lane & 31, lane >> 5
+    ch, rr0 = lane & 7, lane >> 3
+    f32 = epi == E.ELIS_EPI_BIAS_RES_F32
+    EB = 4 if f32 else 2
+    written = np.zeros(M * N * EB // 16, np.int32) if full_cover else None
+    for m0, n0 in {(int(a) * BM, int(b) * BN) for a, b in zip(tm, tn)}:
+        rows = min(M - m0, BM)
+        # direct loads: A within rows [m0, m0 + rows), B within 256 rows of w
+        la, lb = rows * K * 2, BN * K * 2
+        assert m0 * K * 2 + la <= M * K * 2 and n0 * K * 2 + lb <= N * K * 2 and max(la, lb) < 1 << 31
+        for h in range(2):
+            for i in range(2):
+                r = wid * 16 + i * 8 + (lane >> 3)
+                c = ((lane & 7) ^ sw(r)) * 8
+                ra, rb = (r >> 6) * 128 + h * 64 + (r & 63), (r >> 5) * 64 + h * 32 + (r & 31)
+                oa, ob = (ra * K + c) * 2, (rb * K + c) * 2
+                last = (K - BK) * 2 + 16  # the last slab's 16 bytes
+                assert np.array_equal(oa + last <= la, ra < rows) and np.array_equal(oa < la, ra < rows)
+                assert (ob + last).max() <= lb and rb.max() < BN
+        # bias (and LayerNorm g, b) of a wave's 64 columns: one float a lane, 256 bytes each in its staging area
+        assert (n0 + wn * 64 + lane).max() < N and 3 * 256 <= STG_B
+        for j in range(2):
+            for q in range(4):
+                at = (j * 32 + 8 * q + 4 * kg) * 4
+                assert (at + 16).max() <= 256
+            assert (512 + (j * 32 + ch * 4) * 4 + 16).max() <= 3 * 256  # b, the last of the three
+        # staging: 32 rows of 128 bytes, 16-byte (fp32) or 8-byte (bf16) units
+        for j in range(1 if f32 else 2):
+            for q in range(4):
+                at = rl * 128 + ((((2 * q + kg) ^ sw(rl)) * 16) if f32 else (((4 * j + q) ^ sw(rl)) * 16 + 8 * kg))
+                assert (at + (16 if f32 else 8)).max() <= STG_B
+        # residual reads, row statistics and stores, the running offsets as the kernel keeps them
+        size = (rows * N - n0) * EB
+        base = (m0 * N + n0) * EB
+        assert base + size <= M * N * EB and size < 1 << 31
+        ro0 = ((wm * 128 + rr0) * N + wn * 64) * EB + ch * 16
+        row8 = 8 * N * EB
+
+        def store(off, row):
+            keep = off + 16 <= size
+            assert np.array_equal(keep, row < rows) and np.array_equal(off < size, row < rows)
+            if written is not None:
+                np.add.at(written, (base + off[keep]) // 16, 1)
+
+        if f32:
+            fo, so = ro0.copy(), ro0.copy()
+            for b in range(8):
+                i, j = b >> 1, b & 1
+                if j == 1:
+                    fo = fo - 4 * row8
+                for rr in range(4):
+                    row = wm * 128 + i * 32 + rr * 8 + rr0 + 0 * ch
+                    assert np.array_equal(fo + j * 128, (row * N + wn * 64) * 4 + ch * 16 + j * 128)
+                    assert np.array_equal(fo + j * 128 + 16 <= size, row < rows)
+                    stat = row * 8  # of rows * 8 bytes from row m0
+                    assert np.array_equal(stat + 8 <= rows * 8, row < rows)
+                    fo = fo + row8
+                    store(so + j * 128, row)
+                    so = so + row8
+                if j == 0:
+                    so = so - 4 * row8
+        else:
+            for i in range(4):
+                for rr in range(4):
+                    store(ro0, wm * 128 + i * 32 + rr * 8 + rr0 + 0 * ch)
+                    ro0 = ro0 + row8
+    if written is not None:
+        assert np.all(written == 1), "each output element is stored exactly once"
+
+
+# ----------------------------------------------------------------------------- one-wave kernel
+
+def check_wave(M, N, K, epi, cfg, full_cover):
+    """gemm_wave_kernel<EPI>: 32 x 32 tiles, a ring of eight 64-deep slabs."""
+    RING, SLAB, KT = 8, 64 * BK, K // BK
+    tiles_m, tiles_n = -(-M // 32), N // 32
+    nblk = tiles_m * tiles_n
+    t = xcd_remap(np.arange(nblk), nblk)
+    tm, tn = t % tiles_m, t // tiles_m
+    assert np.array_equal(np.sort(tm * tiles_n + tn), np.arange(nblk))
+    tm, tn = corner_tiles(tm, tn, tiles_m, tiles_n, full_cover)
+    lane = np.arange(WAVE)
+    rl, kg = lane & 31, lane >> 5
+    f32 = epi == E.ELIS_EPI_BIAS_RES_F32
+    # a slab in LDS: four loads of eight rows per operand, each element of the slab once
+    lds = np.full((SLAB // 8, 2), -1)
+    for op in range(2):
+        for i in range(4):
+            r = i * 8 + (lane >> 3)
+            unit = (op * 4 + i) * 64 + lane  # lane i's 16 bytes land at the load's base + 16 i
+            assert np.all(lds[unit, 0] == -1)
+            lds[unit, 0], lds[unit, 1] = op * 32 + r, (lane & 7) ^ sw(r)
+    assert np.all(lds >= 0)
+    for ks in range(4):
+        lo = rl * BK + ((ks * 2 + kg) ^ sw(rl)) * 8
+        for op in range(2):
+            unit = (op * 32 * BK + lo) // 8
+            assert np.array_equal(lds[unit, 0], op * 32 + rl) and np.array_equal(lds[unit, 1], ks * 2 + kg)
+    # the ring: at step kt slabs up to kt are read, slab kt + 7 is requested and slab kt + 1 is waited for and read
+    asked, held = [], {}
+    for kt in range(RING - 1):
+        asked.append(kt)
+        held[kt % RING] = kt
+    read = {0}
+    for kt in range(KT):
+        new = kt + RING - 1
+        assert held.get(new % RING, -1) in read | {-1}, "a slab is loaded over before it was read"
+        held[new % RING] = new
+        asked.append(new)
+        landed = asked[:-(RING - 2)]  # at most (RING - 2) * 8 loads outstanding, eight per slab
+        assert kt + 1 in landed and held[(kt + 1) % RING] == kt + 1
+        read.add(kt + 1)
+    assert (RING - 2) * 8 < 64
+    written = np.zeros(M * N, np.int32) if full_cover else None
+    for m0, n0 in {(int(a) * 32, int(b) * 32) for a, b in zip(tm, tn)}:
+        rows = min(M - m0, 32)
+        m = m0 + np.minimum(rl, rows - 1)
+        for q in range(4):
+            n = n0 + 8 * q + 4 * kg
+            assert (n + 4).max() <= N  # bias, LayerNorm g, b
+            assert (m0 * N + n0 + (m - m0) * N + (n - n0) + 4).max() <= M * N and m.max() < M  # residual
+        assert ((m - m0) * 8 + 8).max() <= rows * 8 and m0 + rows <= M  # statistics, of rows * 8 bytes
+        la, lb = rows * K * 2, 32 * K * 2
+        assert m0 * K * 2 + la <= M * K * 2 and n0 * K * 2 + lb <= N * K * 2 and max(la, lb) < 1 << 31
+        for i in range(4):
+            r = i * 8 + (lane >> 3)
+            c = ((lane & 7) ^ sw(r)) * 8
+            oa, ob = (np.minimum(r, rows - 1) * K + c) * 2, (r * K + c) * 2
+            assert (oa + (K - BK) * 2 + 16).max() <= la and (ob + (K - BK) * 2 + 16).max() <= lb
+        keep = rl < rows
+        for q in range(4):
+            o = m * N + n0 + 8 * q + 4 * kg
+            assert (o[keep] + 4).max() <= M * N
+            if written is not None:
+                for e in range(4):
+                    np.add.at(written, o[keep] + e, 1)
+    if written is not None:
+        assert np.all(written == 1)
+
+
+CHECKS = {"sched": check_sched, "reg": check_reg, "persist": check_persist, "wave": check_wave}
+
+
 def check_config(cid, M, N, K, epi, full_cover):
     cfg = CONFIGS[cid]
+    if cfg[0] == "persist" and K < 2 * BK:
+        cfg = CONFIGS[32]
     assert N % cfg[2] == 0 and K % BK == 0
-    (check_sched if cfg[0] == "sched" else check_reg)(M, N, K, epi, cfg, full_cover)
+    CHECKS[cfg[0]](M, N, K, epi, cfg, full_cover)
 
 
 SMALL_M = [1, 2, 31, 32, 33, 63, 64, 65, 127, 129, 255, 256, 257, 300, 511, 513]
@@ -318,8 +530,9 @@ SMALL_M = [1, 2, 31, 32, 33, 63, 64, 65, 127, 129, 255, 256, 257, 300, 511, 513]
 def test_every_configuration_small_sizes_exact_cover(cid, epi):
     bn = CONFIGS[cid][2]
     N = 192 if cid == 1 else 2 * max(bn, 128)
-    for M in SMALL_M:
-        check_config(cid, M, N, 128, epi, full_cover=True)
+    for K in (64, 128, 192):
+        for M in SMALL_M if K == 128 else (1, 257):
+            check_config(cid, M, N, K, epi, full_cover=True)
 
 
 # The plan sweep's sizes: M = 1K .. 92K for the encoder shapes (N, K) of BERT-base and XLM-R-large.
@@ -337,11 +550,15 @@ def lib():
     return E.lib()
 
 
+FEW_M = [1, 16, 31, 33, 64, 150, 193, 200, 300, 511, 540]  # rows that 32 x 32 tiles are chosen for, by shape
+
+
 @pytest.mark.parametrize("n,k", SHAPES)
 def test_chosen_plans_stay_in_bounds(lib, n, k):
     checked = 0
     for epi in EPIS:
-        for M in SWEEP_M:
+        assert TILE_TO_CFG[E.elis_linear_plan(33, n, k, epi)[1][:3]] == 40
+        for M in FEW_M + SWEEP_M:
             st, plan = E.elis_linear_plan(M, n, k, epi)
             assert st == E.ELIS_OK
             main = TILE_TO_CFG[(plan[0], plan[1], plan[2])]
@@ -355,13 +572,14 @@ def test_chosen_plans_stay_in_bounds(lib, n, k):
                 check_config(rest, M - m1, n, k, epi, full_cover=False)
                 assert m1 + (M - m1) == M
             checked += 1
-    assert checked == len(EPIS) * len(SWEEP_M)
+    assert checked == len(EPIS) * len(FEW_M + SWEEP_M)
 
 
-@pytest.mark.parametrize("cid", [21, 32, 33, 34, 35, 36])
+@pytest.mark.parametrize("cid", [21, 32, 33, 34, 35, 36, 40])
 def test_each_configuration_at_the_largest_sizes(cid):
     """The large tiles at the largest token counts; the 64-row tiles (planned over at most four rounds
-    of 256 compute units) at the largest M that fits in four rounds, and one row of tiles past it."""
+    of 256 compute units) at the largest M that fits in four rounds, and one row of tiles past it, the
+    32-row tiles (one round) likewise."""
     _, bm, bn, _, _, _, occ, _ = CONFIGS[cid]
     for n, k in SHAPES:
         if n % bn:
@@ -369,7 +587,7 @@ def test_each_configuration_at_the_largest_sizes(cid):
         if bm >= 128:
             sizes = (92233, 109400)
         else:
-            m4 = 4 * occ * 256 // (n // bn) * bm
+            m4 = (1 if cid == 40 else 4) * occ * 256 // (n // bn) * bm
             sizes = (m4, m4 + 1)
         for M in sizes:
             check_config(cid, M, n, k, E.ELIS_EPI_BIAS_RES_F32, full_cover=False)

@@ -112,8 +112,8 @@ def test_same_bits_as_small_tiles(m, n, k, epi):
 @pytest.mark.parametrize("m,n,k", [(1, 128, 64), (31, 128, 128), (32, 256, 448), (33, 384, 512), (65, 128, 576), (193, 768, 3072),
                                    (512, 1024, 320)])
 def test_few_rows_same_bits_as_small_tiles(m, n, k, epi):
-    """32 x 32 tiles (the library's choice at these sizes), from one slab to more than the ring of eight,
-    against 64 x 64 tiles."""
+    """32 x 32 tiles, from one slab to more than the ring of eight (1, 2, 5, 7, 8, 9 and 48), against 64 x 64
+    tiles and the library's own choice."""
     import torch
     from tests.gpu_util import note, ok, stream
     note(f"few rows m={m} n={n} k={k} epi={epi}")
@@ -124,11 +124,11 @@ def test_few_rows_same_bits_as_small_tiles(m, n, k, epi):
     f32 = epi == E.ELIS_EPI_BIAS_RES_F32
     res = torch.randn((m, n), generator=gen, device="cuda", dtype=torch.float32) if f32 else None
     outs = []
-    for plan in (None, (64, 64, 2, m, 0, 0, 0)):
+    for plan in ((32, 32, 2, m, 0, 0, 0), (64, 64, 2, m, 0, 0, 0), None):
         out = torch.full((m * n + 4096,), 7.0, dtype=torch.float32 if f32 else torch.bfloat16, device="cuda")
         args = (x.data_ptr(), w.data_ptr(), bias.data_ptr(), res.data_ptr() if f32 else None, m, n, k, epi)
         ok(E.elis_linear(*args, out.data_ptr(), stream()) if plan is None else E.elis_linear_with_plan(*args, plan, out.data_ptr(), stream()))
         torch.cuda.synchronize()
         assert bool((out[m * n:] == 7.0).all())
         outs.append(out[:m * n].view(torch.int32 if f32 else torch.int16))
-    assert torch.equal(outs[0], outs[1])
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
