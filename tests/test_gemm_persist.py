@@ -132,3 +132,50 @@ def test_few_rows_same_bits_as_small_tiles(m, n, k, epi):
         assert bool((out[m * n:] == 7.0).all())
         outs.append(out[:m * n].view(torch.int32 if f32 else torch.int16))
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,d_ff,heads,sizes", [(256, 320, 4, (8003, 33001, 65537)), (512, 1024, 8, (2000, 8000, 16001, 33003, 66001))])
+def test_residual_norm_epilogues_same_bits_in_every_tile(d, d_ff, heads, sizes):
+    """The epilogues that rebuild a LayerNorm output as the residual (out-projection and second feed-forward
+    product) are reached through the encoder only: the same sequences' final hidden states, alone (32 x 32 tiles) and at
+    both ends of batches whose products run in every other tile, the persistent one over one and several tiles
+    per work-group and with a ragged last tile among them. Alone they are checked against the oracle."""
+    import torch
+
+    import oracle
+    from paper_2505_09142_amd.device import DeviceWeights, Predictor, upload_batch
+    from tests.gpu_util import note
+    from workloads import make_weights, pack
+    from workloads.configs import EncoderShape
+    shape = EncoderShape("residual_norm", 2, d, heads, d_ff, 1000, 512, 1, 0, True)
+    W = make_weights(shape, d)
+    pr = Predictor(DeviceWeights(shape, W.device))
+    rng = np.random.default_rng(d)
+    own = [rng.integers(1, 1000, L).astype(np.int32) for L in (61, 1, 33)]
+    rows = sum(len(s) for s in own)
+
+    def hidden(seqs):
+        b = pack(seqs)
+        ids, cu, _ = upload_batch(b)
+        pred, hid = pr.predict(ids, cu, b.max_seqlen, want_hidden=True)
+        assert pr.status() == (E.ELIS_OK, 0)
+        return b, pred, hid
+
+    b, pred, alone = hidden(own)
+    ref_p, ref_h = oracle.oracle_forward(b.token_ids, b.cu_seqlens, W.master, shape)
+    assert float(np.abs(alone.cpu().numpy() - ref_h).max()) <= 5e-2 and np.all(np.abs(pred.cpu().numpy() - ref_p) <= 2e-2 * np.maximum(np.abs(ref_p), 1))
+    tiles = set()
+    for T in (rows,) + sizes:
+        for k in (d, d_ff):
+            p = E.elis_linear_plan(T, d, k, E.ELIS_EPI_BIAS_RES_F32)[1]
+            tiles |= {p[:2]} | ({p[4:6]} if p[3] < T else set())
+    assert {(32, 32), (64, 64), (256, 256)} <= tiles
+    for T in sizes:
+        note(f"residual-norm epilogues d={d} T={T}")
+        fill, extra = T - 2 * rows, []
+        while fill > 0:
+            extra.append(rng.integers(1, 1000, min(fill, 500)).astype(np.int32))
+            fill -= len(extra[-1])
+        _, _, hid = hidden(own + extra + own)
+        assert torch.equal(hid[:rows], alone) and torch.equal(hid[T - rows:], alone), T
