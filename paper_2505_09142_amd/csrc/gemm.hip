@@ -825,13 +825,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // ---------------------------------------------------------------------------------------------
 // 32 x 32 tiles, one wave per work-group: products of few rows, where a wider tile would leave most
-// CUs without one. The wave keeps seven 64-deep k-slabs (8 KB each) in flight into a ring of eight in
+// CUs without one. The wave keeps six or seven 64-deep k-slabs (8 KB each) in flight into a ring of eight in
 // LDS; nobody else reads them, so there is no barrier. Fragments of the next slab are read while the
 // current one is multiplied, and the residual, bias and LayerNorm columns are requested up front.
-// Bound by the CU's load path (8 KB per slab at about 37 bytes a cycle, 0.105 us; it takes 0.125):
+// Bound by the CU's load path (8 KB per slab at about 37 bytes a cycle, 0.105 us; it takes 0.126):
 // the 64 x 64 tile moves 16 KB per slab on a quarter of the CUs. That tile (four-stage, 0.22 us per
-// slab) took 13.1 us at 193 x 768 x 3,072, this one 8.9; 64 rows 13.0 -> 8.7, 512 rows 13.7 -> 9.7;
-// 193 x 768 x 768 5.4 -> 4.3. Past 512 tiles (two per CU) the wider tiles win: 193 x 3,072 x 768, 672
+// slab) took 13.7 us at 200 x 768 x 3,072, this one 8.9; 64 rows 13.2 -> 8.6, 520 rows 14.4 -> 11.6;
+// 200 x 768 x 768 5.4 -> 4.2. Past 512 tiles (two per CU) the wider tiles win: 193 x 3,072 x 768, 672
 // tiles, 5.5 against 7.8.
 template <int EPI>
 __global__ __launch_bounds__(64) void gemm_wave_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
@@ -911,14 +911,19 @@ __global__ __launch_bounds__(64) void gemm_wave_kernel(const uint16_t* __restric
     for (int p = 0; p < RING - 1; ++p) load(p);
     wait_vmcnt<(RING - 2) * 8>();
     read(0, 0);
-    // Slab kt: request slab kt + 7 (into the slot of slab kt - 1, whose fragments have been multiplied),
-    // wait for slab kt + 1 and read its fragments, multiply.
+    // Slab kt: wait for slab kt + 1 and read its fragments, request slab kt + 7 (into the slot of slab kt - 1, whose
+    // fragments have been multiplied, hence read), multiply. The barriers keep the compiler to this order: left alone
+    // it read every second slab's fragments only in front of their products, and nothing but its own schedule kept
+    // a read ahead of the load over its slot. (Requesting before reading exposes the reads: 8.9 -> 9.9 us at
+    // 193 x 768 x 3,072.)
     auto step = [&](int buf, int kt) {
-        load(kt + RING - 1);
-        wait_vmcnt<(RING - 2) * 8>();
+        wait_vmcnt<(RING - 3) * 8>();
         read(buf ^ 1, kt + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        load(kt + RING - 1);
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) acc = Mfma<32>::run(fb[buf][ks], fa[buf][ks], acc);
+        __builtin_amdgcn_sched_barrier(0);
     };
     int kt = 0;
     for (; kt + 1 < KT; kt += 2) {

@@ -469,20 +469,19 @@ def check_wave(M, N, K, epi, cfg, full_cover):
         for op in range(2):
             unit = (op * 32 * BK + lo) // 8
             assert np.array_equal(lds[unit, 0], op * 32 + rl) and np.array_equal(lds[unit, 1], ks * 2 + kg)
-    # the ring: at step kt slabs up to kt are read, slab kt + 7 is requested and slab kt + 1 is waited for and read
+    # the ring: at step kt slab kt + 1 is waited for and read, slab kt + 7 requested, slab kt multiplied
     asked, held = [], {}
     for kt in range(RING - 1):
         asked.append(kt)
         held[kt % RING] = kt
-    read = {0}
+    assert asked[:-(RING - 2)] == [0]  # read ahead of the loop, (RING - 2) * 8 loads outstanding, eight per slab
     for kt in range(KT):
+        landed = asked[:-(RING - 3)]  # at most (RING - 3) * 8 outstanding
+        assert landed[-1] == kt + 1 and held[(kt + 1) % RING] == kt + 1
         new = kt + RING - 1
-        assert held.get(new % RING, -1) in read | {-1}, "a slab is loaded over before it was read"
+        assert held.get(new % RING, -1) == kt - 1, "a slab is loaded over before its fragments were multiplied"
         held[new % RING] = new
         asked.append(new)
-        landed = asked[:-(RING - 2)]  # at most (RING - 2) * 8 loads outstanding, eight per slab
-        assert kt + 1 in landed and held[(kt + 1) % RING] == kt + 1
-        read.add(kt + 1)
     assert (RING - 2) * 8 < 64
     written = np.zeros(M * N, np.int32) if full_cover else None
     for m0, n0 in {(int(a) * 32, int(b) * 32) for a, b in zip(tm, tn)}:
