@@ -449,7 +449,7 @@ def check_wave(M, N, K, epi, cfg, full_cover):
     tiles_m, tiles_n = -(-M // 32), N // 32
     nblk = tiles_m * tiles_n
     t = xcd_remap(np.arange(nblk), nblk)
-    tm, tn = t % tiles_m, t // tiles_m
+    tm, tn = (t // tiles_n, t % tiles_n) if M > N else (t % tiles_m, t // tiles_m)
     assert np.array_equal(np.sort(tm * tiles_n + tn), np.arange(nblk))
     tm, tn = corner_tiles(tm, tn, tiles_m, tiles_n, full_cover)
     lane = np.arange(WAVE)
