@@ -1093,15 +1093,20 @@ namespace {
 // medians of repeated timings over K = 768, 1024, 3072, 4096, the three epilogue kinds and ten
 // fills from a lone tile to four rounds, two sets of operands in turn (so that a product does not
 // find its weights and activations in the L2, as inside the encoder; a fit with everything L2-hot
-// had priced a lone two-stage 64 x 64 tile at half of what it takes there). Fit error: 2-8%, except the
-// lone tiles of the two-stage configurations (up to 26%, never the cheapest choice there).
+// had priced a lone two-stage 64 x 64 tile at half of what it takes there), then moved to where the choice among
+// plans loses least, over 11,500 random products (k = 512 .. 4,096, up to 100,000 rows) with every plan timed.
+// Depths below 512 have a fit of their own (kShallowModel): few slabs hide little of the prologue, and large
+// outputs are bound by memory. Over 12,000 other random products the chosen plan takes 0.3-0.5% more than the best
+// one in the mean (with one fit for all depths 0.9%, up to 1.4 times the best at k = 128), and 1.1% of them
+// are more than 3% slower than the plan the L2-hot fit chooses (4.8%); most of those are GELU
+// products in 64 x 64 tiles, among them n = 3,072, k = 768 at 330 to 470 rows (6.6 us, 7.1 as chosen).
 // A launch whose tiles fill R rounds of work-group slots (work-groups per CU x CUs), the last
 // one a fraction f full, takes part(f) for R = 1, else t1 + (R - 2) * beta + part(f)
 // - (t1 - beta) * f; part is piecewise linear through lat (a lone tile, f -> 0), th (f = 1/2)
 // and t1 (f = 1), beta is the cost of one more full round. Each quantity is a + s * K / 64: the
 // slope per 64-deep k-slab is shared by the epilogue kinds, the intercept is per kind (bf16,
 // bf16 + GELU, fp32 + residual). Full rounds of 256 x 256 tiles cost more per slab than a lone
-// tile (1.6-1.8 against 1.0 us): with every matrix core busy the clock falls to about 1.7 GHz.
+// tile (1.4-1.8 against 1.0 us): with every matrix core busy the clock falls to about 1.7 GHz.
 // The 64-row tiles are priced only up to the four rounds they were timed on and are not offered
 // past that.
 struct TileModel {
@@ -1109,23 +1114,40 @@ struct TileModel {
     float s[4];     // lat, th, t1, beta: slope per k-slab
     float a[3][4];  // intercept per epilogue kind
 };
-constexpr TileModel kTileModels[] = {
-    {21, 256, 256, 1, 0, {1.009f, 1.150f, 1.614f, 1.765f},
-     {{5.05f, 6.28f, 8.18f, 1.99f}, {9.49f, 9.77f, 9.86f, 5.44f}, {8.25f, 14.11f, 26.44f, 17.76f}}},
-    {32, 128, 128, 2, 0, {0.583f, 0.648f, 1.009f, 1.180f},
-     {{2.60f, 3.33f, 3.75f, 0.91f}, {4.27f, 4.83f, 5.72f, 2.55f}, {4.22f, 7.72f, 11.39f, 11.14f}}},
-    {33, 64, 128, 2, 4, {0.354f, 0.514f, 0.605f, 0.770f},
-     {{2.62f, 2.92f, 3.73f, -0.52f}, {4.32f, 3.71f, 4.22f, 0.59f}, {4.06f, 5.05f, 6.94f, 4.36f}}},
-    {34, 64, 128, 1, 4, {0.321f, 0.333f, 0.367f, 0.372f},
-     {{2.86f, 3.07f, 3.44f, 1.58f}, {3.87f, 3.71f, 4.02f, 2.14f}, {3.56f, 4.26f, 5.65f, 3.58f}}},
-    {35, 64, 64, 4, 4, {0.305f, 0.456f, 0.771f, 0.869f},
-     {{1.42f, 2.95f, 3.70f, -1.34f}, {2.71f, 3.17f, 3.50f, -0.58f}, {2.95f, 4.49f, 4.95f, 3.62f}}},
-    {36, 64, 64, 2, 4, {0.218f, 0.237f, 0.377f, 0.380f},
-     {{2.83f, 2.93f, 3.18f, 1.29f}, {3.29f, 3.07f, 3.61f, 1.50f}, {3.35f, 3.86f, 4.78f, 2.16f}}},
+struct LaunchModel {
+    TileModel tiles[6];
+    TileModel wave;  // the one-wave 32 x 32 tile: up to one round, and never beside another launch (beta unused)
 };
-// The one-wave 32 x 32 tile, up to one round and never beside another launch (beta unused).
-constexpr TileModel kWaveModel = {kWaveCfg, 32, 32, 2, 1, {0.125f, 0.126f, 0.176f, 0.f},
-                                  {{2.62f, 2.83f, 2.66f, 0.f}, {2.88f, 3.09f, 2.94f, 0.f}, {2.68f, 2.82f, 3.04f, 0.f}}};
+constexpr LaunchModel kDeepModel = {{
+    {21, 256, 256, 1, 0, {1.009f, 1.150f, 1.420f, 1.765f},
+     {{5.05f, 6.28f, 8.18f, 1.99f}, {9.49f, 9.77f, 9.86f, 5.44f}, {8.25f, 14.11f, 26.44f, 15.63f}}},
+    {32, 128, 128, 2, 0, {0.618f, 0.648f, 1.070f, 1.180f},
+     {{2.60f, 3.33f, 3.75f, 0.91f}, {4.27f, 4.83f, 4.73f, 2.55f}, {4.22f, 7.72f, 11.39f, 9.80f}}},
+    {33, 64, 128, 2, 4, {0.354f, 0.576f, 0.605f, 0.770f},
+     {{2.62f, 2.92f, 3.73f, -0.52f}, {4.32f, 3.46f, 4.22f, 0.59f}, {4.06f, 4.11f, 6.29f, 3.84f}}},
+    {34, 64, 128, 1, 4, {0.321f, 0.304f, 0.367f, 0.372f},
+     {{2.86f, 3.16f, 3.34f, 1.58f}, {3.87f, 3.49f, 3.78f, 2.14f}, {3.56f, 4.00f, 4.97f, 3.58f}}},
+    {35, 64, 64, 4, 4, {0.342f, 0.456f, 0.771f, 0.869f},
+     {{1.25f, 2.60f, 3.26f, -1.34f}, {2.71f, 3.17f, 3.50f, -0.58f}, {2.95f, 4.62f, 4.95f, 3.62f}}},
+    {36, 64, 64, 2, 4, {0.182f, 0.237f, 0.377f, 0.380f},
+     {{2.83f, 3.28f, 3.78f, 1.29f}, {3.46f, 3.07f, 3.61f, 1.50f}, {3.35f, 3.86f, 4.78f, 2.16f}}},
+}, {kWaveCfg, 32, 32, 2, 1, {0.125f, 0.126f, 0.176f, 0.000f},
+    {{2.62f, 2.83f, 2.66f, 0.00f}, {2.88f, 3.09f, 2.94f, 0.00f}, {2.68f, 2.82f, 3.04f, 0.00f}}}};
+constexpr LaunchModel kShallowModel = {{
+    {21, 256, 256, 1, 0, {0.867f, 1.035f, 1.632f, 1.530f},
+     {{4.31f, 5.11f, 7.79f, 4.23f}, {8.83f, 10.05f, 8.07f, 6.63f}, {7.11f, 15.64f, 23.83f, 24.90f}}},
+    {32, 128, 128, 2, 0, {0.418f, 0.487f, 1.173f, 0.892f},
+     {{2.66f, 4.06f, 3.10f, 2.24f}, {2.99f, 5.10f, 4.91f, 3.89f}, {2.17f, 9.56f, 12.35f, 8.45f}}},
+    {33, 64, 128, 2, 4, {0.336f, 0.438f, 0.597f, 0.678f},
+     {{2.37f, 3.17f, 2.87f, 1.00f}, {2.99f, 4.23f, 4.19f, 1.86f}, {2.87f, 5.24f, 8.65f, 4.41f}}},
+    {34, 64, 128, 1, 4, {0.341f, 0.395f, 0.479f, 0.359f},
+     {{2.42f, 3.35f, 2.84f, 1.29f}, {3.07f, 3.66f, 3.49f, 1.91f}, {2.89f, 3.86f, 4.36f, 4.09f}}},
+    {35, 64, 64, 4, 4, {0.197f, 0.364f, 0.698f, 0.667f},
+     {{2.27f, 2.98f, 2.84f, 0.75f}, {2.54f, 3.11f, 3.63f, 1.27f}, {2.37f, 4.33f, 6.37f, 4.67f}}},
+    {36, 64, 64, 2, 4, {0.238f, 0.244f, 0.519f, 0.304f},
+     {{2.23f, 3.14f, 2.88f, 0.72f}, {2.63f, 3.01f, 3.17f, 1.11f}, {2.36f, 3.45f, 4.21f, 2.96f}}},
+}, {kWaveCfg, 32, 32, 2, 1, {0.134f, 0.131f, 0.117f, 0.000f},
+    {{1.73f, 2.65f, 3.18f, 0.00f}, {2.71f, 2.87f, 3.29f, 0.00f}, {2.38f, 2.70f, 3.32f, 0.00f}}}};
 constexpr float kSecondLaunchUs = 1.0f;  // dispatch cost of the remainder launch
 
 int epilogue_kind(int epi) {
@@ -1162,10 +1184,11 @@ GemmPlan plan_gemm(int m, int n, int k, int epi) {
     if (n % 128 != 0) return {1, m, 0};
     const int kind = epilogue_kind(epi);
     const long long cus = device_cus();
+    const LaunchModel& model = k < 512 ? kShallowModel : kDeepModel;
     GemmPlan best{0, m, 0};
     double best_us = -1.0;
     auto fits = [&](const TileModel& t) { return n % t.bn == 0 && (t.cfg != kPersistCfg || gemm_persist_fits(n, k)); };
-    for (const TileModel& main : kTileModels) {
+    for (const TileModel& main : model.tiles) {
         if (!fits(main)) continue;
         const double t = model_us(main, kind, m, n, k, cus);
         if (best_us < 0.0 || t < best_us) {
@@ -1178,7 +1201,7 @@ GemmPlan plan_gemm(int m, int n, int k, int epi) {
         const long long m1 = (tiles / slots) * slots / per_row * main.bm;
         if (m1 <= 0 || m1 >= m) continue;
         const double head = model_us(main, kind, m1, n, k, cus) + kSecondLaunchUs;
-        for (const TileModel& rest : kTileModels) {
+        for (const TileModel& rest : model.tiles) {
             if (rest.cfg == main.cfg || !fits(rest)) continue;
             const double tr = head + model_us(rest, kind, m - m1, n, k, cus);
             if (tr < best_us) {
@@ -1189,7 +1212,7 @@ GemmPlan plan_gemm(int m, int n, int k, int epi) {
     }
     // 32 x 32 tiles where they fill at most one round (512 tiles) and the model prices them lower: up to about 540 rows
     // at n = 768 or 1,024, 200 at n = 2,304 and 150 at n = 3,072 or 4,096.
-    if (gemm_wave_fits(n, k) && model_us(kWaveModel, kind, m, n, k, cus) < best_us) best = {kWaveCfg, m, 0};
+    if (gemm_wave_fits(n, k) && model_us(model.wave, kind, m, n, k, cus) < best_us) best = {kWaveCfg, m, 0};
     return best;
 }
 
