@@ -1126,7 +1126,7 @@ constexpr LaunchModel kDeepModel = {{
     {33, 64, 128, 2, 4, {0.354f, 0.576f, 0.605f, 0.770f},
      {{2.62f, 2.92f, 3.73f, -0.52f}, {4.32f, 3.46f, 4.22f, 0.59f}, {4.06f, 4.11f, 6.29f, 3.84f}}},
     {34, 64, 128, 1, 4, {0.321f, 0.304f, 0.367f, 0.372f},
-     {{2.86f, 3.16f, 3.34f, 1.58f}, {3.87f, 3.49f, 3.78f, 2.14f}, {3.56f, 4.00f, 4.97f, 3.58f}}},
+     {{2.86f, 3.16f, 3.34f, 1.58f}, {3.87f, 3.49f, 3.78f, 2.14f}, {3.56f, 4.00f, 5.50f, 3.58f}}},
     {35, 64, 64, 4, 4, {0.342f, 0.456f, 0.771f, 0.869f},
      {{1.25f, 2.60f, 3.26f, -1.34f}, {2.71f, 3.17f, 3.50f, -0.58f}, {2.95f, 4.62f, 4.95f, 3.62f}}},
     {36, 64, 64, 2, 4, {0.182f, 0.237f, 0.377f, 0.380f},
