@@ -381,7 +381,8 @@ def summarize_issue(csv_path, command):
 
 TRACE_PROFILE = os.path.join(ROOT, "profiles", "bert_base_b64_kernel_trace.md")
 _ROLES = {"seqmap_kernel": "sequence table", "seqmap_direct_kernel": "sequence table", "embed_ln_kernel<3>": "embedding + LN",
-          "select_rank_kernel<16, PlainJobs>": "ISRTF select", "head_tile_kernel<0, true, 8>": "head 768->256 + ReLU (CLS rows)",
+          "select_few_kernel<PlainJobs>": "ISRTF select",
+          "head_tile_kernel<0, true, 8, 4, true>": "head 768->256 + ReLU (CLS rows)",
           "head_out_kernel": "head 256->1, affine", COPY_KERNEL: "(torch copies)"}
 
 

@@ -535,9 +535,10 @@ __global__ __launch_bounds__(WM* WN* kWave) __attribute__((amdgpu_waves_per_eu(O
 // What bounds it. On full rounds of a large square product the board's power limit: 8192 x 8192 x 8192 runs at
 // 1,410 TFLOP/s with normal operands (clock 1.6 GHz) and 1,980 with zeros (2.27 GHz), 80% of the matrix cores'
 // cycles both times. Where the last round is part-filled, that round: 92,000 x 1,024 x 4,096 is 5.63 rounds and
-// hipBLASLt, which splits k over the last one, takes 0.89 times the time on the same box. At k = 768 the epilogues take a quarter of the time (GELU's vector work and the
-// stores; with both left out 93,014 x 3,072 x 768 takes 342 us). Against the one-tile-per-launch
-// kernel with whole-slab waits that it replaces, in us (fp32 out with residual for n = 768):
+// hipBLASLt, which splits k over the last one, takes 0.86-0.89 times the time (two boxes). At k = 768 the
+// epilogues take a quarter of the time (GELU's vector work and the stores; with both left out
+// 93,014 x 3,072 x 768 takes 342 us). Against the one-tile-per-launch kernel with whole-slab waits that it
+// replaces, in us (fp32 out with residual for n = 768):
 //   93,014 x 3,072 x 768 + GELU 489 -> 446    93,014 x 2,304 x 768 315 -> 284
 //   93,014 x 768 x 3,072        483 -> 453    21,760 x 3,072 x 768 + GELU 113 -> 104
 //   102,548 x 1,024 x 4,096     863 -> 800    21,760 x 768 x 3,072 100 -> 97

@@ -334,7 +334,9 @@ hipError_t launch_jobs_append(JobTable t, const int32_t* slots, const int32_t* o
     // 16,384 jobs of 1 / 50 tokens 9.2 / 9.5 us by work-groups and 6.7 / 11.2 by tokens, 65,536 jobs 31 / 40 and
     // 8.2 / 43, 4,096 jobs 4.0 / 4.0 and 6.3 / 7.0.
     if (m > 8192 && total < 32LL * m) {
-        if (total > 0) ELIS_TRY(launch_kernel(jobs_append_tokens_kernel, grid_for(total), dim3(kThreads), 0, st, t, slots, off, tokens, m, total));
+        if (total > 0)
+            ELIS_TRY(launch_kernel(jobs_append_tokens_kernel, grid_for(total), dim3(kThreads), 0, st, t, slots, off, tokens, m,
+                               total));
         return launch_kernel(jobs_len_kernel, grid_for(m), dim3(kThreads), 0, st, t, slots, off, m);
     }
     return launch_kernel(jobs_append_kernel, dim3(m), dim3(kThreads), 0, st, t, slots, off, tokens, total);

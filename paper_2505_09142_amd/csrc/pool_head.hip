@@ -272,8 +272,8 @@ hipError_t fc_tile(const float* in, const float* hidden, const float* z, const i
     };
     // LDS for the steps a wave has, no more: with room for eight of them a CU holds one work-group whatever the depth.
     const int steps = K / (16 * NW);
-    const uintptr_t rows = reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(POOLED && pooling == ELIS_POOL_CLS ? hidden : POOLED ? z : in);
-    if (rows & 15u) return go(head_tile_kernel<ACT, POOLED, NW, 1, false>);
+    const float* x = !POOLED ? in : pooling == ELIS_POOL_CLS ? hidden : z;
+    if ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(x)) & 15u) return go(head_tile_kernel<ACT, POOLED, NW, 1, false>);
     if (steps >= 8) return go(head_tile_kernel<ACT, POOLED, NW, 8, true>);
     if (steps >= 4) return go(head_tile_kernel<ACT, POOLED, NW, 4, true>);
     if (steps >= 2) return go(head_tile_kernel<ACT, POOLED, NW, 2, true>);
