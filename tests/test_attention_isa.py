@@ -6,7 +6,7 @@ explicit vmcnt wait) only before the next barrier. The compiler tracks such dire
 loads by LDS variable: when both buffers were one array it could not tell the buffer being
 loaded from the one being read, and put a vmcnt(0) wait before the first LDS read of every
 tile, so each tile waited out the next one's loads. This test compiles attention.hip for gfx950
-with the library's flags and checks, in the all-queries kernel and the CLS-only one, that between
+with the library's flags and checks, in the all-queries kernel, the CLS-only one and the narrow one, that between
 a direct-to-LDS load and the next barrier no LDS read is preceded by a vmcnt wait.
 """
 import os
@@ -18,9 +18,10 @@ import pytest
 
 from paper_2505_09142_amd import build as B
 
-KERNELS = {  # all queries; the CLS-only tail of the last layer
+KERNELS = {  # all queries; the CLS-only tail of the last layer; one 16-query block per wave
     "all": "_ZN4elis12_GLOBAL__N_116attention_kernelILi64ELb0EEEvPKtPKiS5_S5_iPtfi",
     "cls": "_ZN4elis12_GLOBAL__N_116attention_kernelILi64ELb1EEEvPKtPKiS5_S5_iPtfi",
+    "narrow": "_ZN4elis12_GLOBAL__N_123attention_narrow_kernelILi64EEEvPKtPKiS5_S5_iPtfi",  # launches of few work-groups
 }
 DMA = re.compile(r"^\s*(buffer_load_dword\S*\s.*\blds\b|global_load_lds_dword\S*)")
 WAIT = re.compile(r"^\s*s_waitcnt\s.*vmcnt\(")
